@@ -108,6 +108,56 @@ static float guess_bound(const float *e, int nb, float lo, float iw) {
     return t;
 }
 
+// The smallest pt >= 0 with pt * smax > jet_pt in float32 (the product's
+// rounding is monotone in pt, so the jets that can be selected are those at or
+// above it); -inf when jet_pt < 0 (or NaN), NaN when there is none.
+static float pt_floor(float jet_pt, float smax) {
+    if (!(jet_pt >= 0.0f)) return -INFINITY;
+    auto at = [](uint32_t bits) {
+        float f;
+        std::memcpy(&f, &bits, sizeof f);
+        return f;
+    };
+    uint32_t lo = 0u, hi = 0x7f800000u;  // not selected at lo (0), selected at hi (inf)
+    if (!(at(hi) * smax > jet_pt)) return std::nanf("");
+    while (hi - lo > 1u) {
+        const uint32_t m = lo + (hi - lo) / 2u;
+        (at(m) * smax > jet_pt ? hi : lo) = m;
+    }
+    return at(hi);
+}
+
+// A lower bound of the pt >= 0 with pt * (1 + s * d) > jet_pt for some shift s
+// of the query and the table's d at that pt in some row: interval by interval
+// of the pt bins' centres, where d lies between the two values; every factor
+// widened by 1e-5 (its rounding, relative to 1 + |s| * |d|, is below 1e-6).
+// -inf (every jet a candidate) when a factor may not be positive or a value is
+// not finite: then energies are not bounded this way.
+static float pt_floor_shifted(const hepk_query &Q, float smin, float smax) {
+    if (!(Q.jet_pt >= 0.0f)) return -INFINITY;
+    const int nr = Q.jes_n_eta, nc = Q.jes_n_pt;
+    auto centre = [&](int i) { return static_cast<double>(bin_centre(Q.jes_pt_edges[i], Q.jes_pt_edges[i + 1])); };
+    double best = INFINITY;
+    for (int k = 0; k <= nc; ++k) {  // [centre k - 1, centre k], open at both ends of the table
+        const double a = k == 0 ? 0.0 : centre(k - 1), b = k == nc ? INFINITY : centre(k);
+        double fmax = -INFINITY, fmin = INFINITY;
+        for (int r = 0; r < nr; ++r)
+            for (int c = std::max(k - 1, 0); c <= std::min(k, nc - 1); ++c) {
+                const double d = Q.jes_delta[static_cast<int64_t>(r) * nc + c];
+                if (!std::isfinite(d)) return -INFINITY;
+                for (const double s : {static_cast<double>(smin), static_cast<double>(smax)}) {
+                    const double m = 1e-5 * (1.0 + std::fabs(s * d));
+                    fmax = std::max(fmax, 1.0 + s * d + m);
+                    fmin = std::min(fmin, 1.0 + s * d - m);
+                }
+            }
+        if (!(fmin > 0.0) || !std::isfinite(fmax)) return -INFINITY;
+        const double t = std::max(std::max(a, 0.0), Q.jet_pt / fmax);
+        if (t <= b) best = std::min(best, t);
+    }
+    return std::max(0.0f, std::nextafter(static_cast<float>(best * (1.0 - 1e-6)), -INFINITY));
+}
+
 // Fills the query-dependent fields of a table entry; the caller has checked q.
 static void set_qdev(QDev &o, const hepk_query &Q, const float *const edges[3]) {
     o.mu_pt = Q.mu_pt;
@@ -129,6 +179,7 @@ static void set_qdev(QDev &o, const hepk_query &Q, const float *const edges[3]) 
         o.smax = std::max(o.smax, Q.scales[v]);
         o.smin = std::min(o.smin, Q.scales[v]);
     }
+    o.ptmin = pt_floor(Q.jet_pt, o.smax);
     o.active = 1;
     // lookup tables: placed by the plan (lk_place); absent until then
     o.pu_nb = o.sf_nb = o.jr_nb = o.jc_nb = 0;
@@ -219,6 +270,7 @@ static void lk_place(QDev &o, const hepk_query &Q, std::vector<float> &tab) {
         o.jr_e = put(Q.jes_eta_edges, Q.jes_n_eta + 1);
         o.jc_nb = Q.jes_n_pt;
         o.jc_e = put(Q.jes_pt_edges, Q.jes_n_pt + 1);
+        o.ptmin = pt_floor_shifted(Q, o.smin, o.smax);
         o.jd = put(Q.jes_delta, static_cast<size_t>(Q.jes_n_eta) * Q.jes_n_pt);
         axis(Q.jes_eta_edges, Q.jes_n_eta, o.jr_lo, o.jr_hi, o.jr_iw);
         axis(Q.jes_pt_edges, Q.jes_n_pt, o.jc_lo, o.jc_hi, o.jc_iw);

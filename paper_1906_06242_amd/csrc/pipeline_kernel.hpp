@@ -28,25 +28,28 @@
 //   2. per query: muon (and electron) lanes evaluate the cuts; the selected
 //      leptons are compacted by wavefront ballot into LDS in tile order,
 //      with the count of selected leptons before each lepton;
-//   3. each event lane writes its event's range of selected leptons over its
-//      jets (an empty range for an event that cannot pass: too few selected
-//      muons, or too few jets before any cut);
-//   4. jet lanes test the cone against those leptons and store pt in LDS, or
-//      NaN when removed, outside |eta|, or below jet_pt at every scale (the
-//      last two skip the test);
-//   5. event lanes walk their jets in order: ptv = pt * s, the jet cut, the
-//      count, the left-to-right float32 H_T, the maximum, the b-tag count;
+//   3. jet lanes mark the candidate jets (inside |eta|, pt above jet_pt at the
+//      largest energy any scale gives it) and write the number of candidates
+//      (and b-tagged candidates) before each jet; event lanes read both ends
+//      of their ranges and keep the events that can still pass: enough
+//      selected muons, candidates and b-tagged candidates (cuts only remove
+//      jets, so no other event can);
+//   4. the candidates of those events alone are compacted into LDS, and the
+//      cone test runs over that dense list, a lane per candidate: most jets
+//      of a tile never reach it (base selection: 86 of 320, with a b-tag 47);
+//   5. event lanes walk their candidates in order: ptv = pt * s, the jet cut,
+//      the count, the left-to-right float32 H_T, the maximum, the b-tag count;
 //      then the event cut and three fills into the workgroup's LDS
 //      histograms (float64 sums, uint32 counts).  With several jet-energy
 //      scales a lane takes an (event, group of kG scales) pair instead and
 //      one walk serves the group.  The bins of all of a lane's fills are
-//      found together (guesses, then every edge read, then the check).
+//      found together.
 // Steps 2-5 exchange data through the wavefront's own LDS region; a
 // wavefront's LDS operations complete in issue order, so only compiler
 // ordering fences are needed between them.  A tile whose objects exceed the
-// register capacity (a 5-sigma fluctuation for the paper's multiplicities,
-// always possible for arbitrary input) is processed one lane per event
-// straight from HBM with the same arithmetic.
+// register capacity (a 3.5-sigma fluctuation for the paper's multiplicities,
+// always possible for arbitrary input) runs as smaller sub-tiles; a single
+// event beyond it is read straight from HBM, with the same arithmetic.
 #pragma once
 
 #include <algorithm>
@@ -77,6 +80,10 @@ struct QDev {
     int32_t min_mu, min_jet, min_b;
     int32_t n_scale, scale0;
     float smax;          // largest scale; used only when jet_pt >= 0
+    // A jet with pt < ptmin (or NaN) is selected at no scale: the smallest pt
+    // with pt * smax > jet_pt (with shifted energies a lower bound of it over
+    // the table); -inf when jet_pt < 0, NaN when no pt is selected.
+    float ptmin;
     int32_t active;      // 0: idle query slot, skipped
     int32_t nbins[3];
     int32_t ebase[3];    // first edge of each observable in the plan's edge table
@@ -213,8 +220,8 @@ __device__ __forceinline__ X pin(X x) {
 }
 
 // All fields are read first and pinned by one statement, so their loads are
-// issued together and waited for once (the guess bounds only with CERT).
-template <bool LDSH, bool CERT, typename QT>
+// issued together and waited for once.
+template <bool LDSH, typename QT>
 __device__ __forceinline__ FillC fill_consts(const QT &Q) {
     FillC F;
     F.base = LDSH ? Q.lslot0 : Q.gslot0;
@@ -227,51 +234,25 @@ __device__ __forceinline__ FillC fill_consts(const QT &Q) {
         F.lo[h] = Q.lo[h];
         F.hi[h] = Q.hi[h];
         F.iw[h] = Q.inv_w[h];
-        F.ck[h] = CERT ? Q.chk[h] : 0.0f;
+        F.ck[h] = Q.chk[h];
     }
     asm volatile(""
                  : "+s"(F.base), "+s"(F.per), "+s"(F.nb[0]), "+s"(F.nb[1]), "+s"(F.nb[2]), "+s"(F.eb[0]),
                    "+s"(F.eb[1]), "+s"(F.eb[2]), "+s"(F.off[0]), "+s"(F.off[1]), "+s"(F.off[2]), "+s"(F.lo[0]),
                    "+s"(F.lo[1]), "+s"(F.lo[2]), "+s"(F.hi[0]), "+s"(F.hi[1]), "+s"(F.hi[2]), "+s"(F.iw[0]),
-                   "+s"(F.iw[1]), "+s"(F.iw[2]));
-    if (CERT) asm volatile("" : "+s"(F.ck[0]), "+s"(F.ck[1]), "+s"(F.ck[2]));
+                   "+s"(F.iw[1]), "+s"(F.iw[2]), "+s"(F.ck[0]), "+s"(F.ck[1]), "+s"(F.ck[2]));
     return F;
 }
 
 // Slots of N values, x[n] going to observable n % 3 (H_T, lead, nJet): the
-// same slot as hist_slot_lohi.  Without CERT every guess from the
-// uniform-bin formula is checked against its bin's edges (one LDS round trip
-// for all N values).  With CERT the guess is taken as exact unless its
-// fraction is within the plan's bound of 0 or 1 (chk), so only lanes with such
-// a guess read edges -- rarely any lane of a wavefront, so the round trip is
-// usually skipped; this pays where a lane fills many values (several scales).
-// Either way a binary search replaces a guess that was off.
-template <int N, bool CERT>
+// same slot as hist_slot_lohi.  The guess from the uniform-bin formula is
+// taken as exact unless its fraction is within the plan's bound of 0 or 1
+// (chk), so only lanes with such a guess read edges -- rarely any lane of a
+// wavefront, so the round trip is usually skipped (eight queries, whose edges
+// stay in HBM: 588 -> 544 us per 6.25e6 events against checking every guess).
+// A binary search replaces a guess that was off.
+template <int N>
 __device__ __forceinline__ void find_bins(const FillC &F, const float *edges, const float (&x)[N], int (&s)[N]) {
-    if (!CERT) {
-        int k[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const int h = n % 3;
-            const float g = (x[n] - F.lo[h]) * F.iw[h];
-            const int gi = g >= 0.0f ? (g < static_cast<float>(F.nb[h]) ? static_cast<int>(g) + 1 : F.nb[h]) : 1;
-            s[n] = !(x[n] >= F.lo[h]) ? 0 : (x[n] >= F.hi[h] ? F.nb[h] + 1 : gi);
-            k[n] = F.eb[h] + ((s[n] >= 1 && s[n] <= F.nb[h]) ? s[n] : 1);
-        }
-        float a[N], b[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            a[n] = edges[k[n] - 1];
-            b[n] = edges[k[n]];
-        }
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const int h = n % 3;
-            if (s[n] >= 1 && s[n] <= F.nb[h] && (x[n] < a[n] || x[n] >= b[n]))
-                s[n] = bin_search(edges + F.eb[h], F.nb[h], x[n]);
-        }
-        return;
-    }
     bool chk = false;  // some value of this lane needs the edges
 #pragma unroll
     for (int n = 0; n < N; ++n) {
@@ -324,74 +305,96 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One event, one lane, columns read straight from HBM.  LK: lookup event
-// weights and, with jes_mode 1, shifted jet energies.
+// Value of x in lane l (l uniform).
+__device__ __forceinline__ float lane_f(float x, int l) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+}
+
+// One event by the whole wavefront, columns read straight from HBM (events
+// beyond the on-chip capacity): a lane per object, 64 at a time, the selected
+// ones then taken in order for the sums and products.  Everything but the
+// lanes' own objects is uniform.  LK: lookup event weights and, with jes_mode
+// 1, shifted jet energies.
 template <typename T, bool EXT, bool LDSH, bool DBG, bool LK>
-__device__ void event_direct(const PipeArgs &P, const DsDev &D, int64_t e, const float *edges,
-                             const HistSink<LDSH, LK> &sink) {
+__device__ __forceinline__ void event_direct(const PipeArgs &P, const DsDev &D, int64_t e, int lane,
+                                             const float *edges, const HistSink<LDSH, LK> &sink) {
     const bool has_iso = D.miso != nullptr;
     const bool has_el = EXT && D.eoff != nullptr;
     const bool has_bt = EXT && D.jbt != nullptr;
-    const float w0 = D.w ? D.w[e] : 1.0f;
-    const int64_t j0 = D.joff[e], j1 = D.joff[e + 1];
-    const int64_t m0 = D.moff[e], m1 = D.moff[e + 1];
-    const int64_t l0 = has_el ? D.eoff[e] : 0, l1 = has_el ? D.eoff[e + 1] : 0;
-    const T *jpt = static_cast<const T *>(D.jpt), *jeta = static_cast<const T *>(D.jeta);
-    const T *jphi = static_cast<const T *>(D.jphi), *jbt = static_cast<const T *>(D.jbt);
-    const T *mpt = static_cast<const T *>(D.mpt), *meta = static_cast<const T *>(D.meta);
-    const T *mphi = static_cast<const T *>(D.mphi), *miso = static_cast<const T *>(D.miso);
-    const T *ept = static_cast<const T *>(D.ept), *eeta = static_cast<const T *>(D.eeta);
-    const T *ephi = static_cast<const T *>(D.ephi);
+    const int64_t j0 = as_const(D.joff)[e], m0 = as_const(D.moff)[e], l0 = has_el ? as_const(D.eoff)[e] : 0;
+    const int64_t nj_all = as_const(D.joff)[e + 1] - j0, nm_all = as_const(D.moff)[e + 1] - m0;
+    const int64_t nl_all = has_el ? as_const(D.eoff)[e + 1] - l0 : 0;
+    const T *jpt = static_cast<const T *>(D.jpt) + j0, *jeta = static_cast<const T *>(D.jeta) + j0;
+    const T *jphi = static_cast<const T *>(D.jphi) + j0, *jbt = static_cast<const T *>(D.jbt) + (has_bt ? j0 : 0);
+    const T *mpt = static_cast<const T *>(D.mpt) + m0, *meta = static_cast<const T *>(D.meta) + m0;
+    const T *mphi = static_cast<const T *>(D.mphi) + m0;
+    const T *miso = static_cast<const T *>(D.miso) + (has_iso ? m0 : 0);
+    const T *ept = static_cast<const T *>(D.ept) + l0, *eeta = static_cast<const T *>(D.eeta) + l0;
+    const T *ephi = static_cast<const T *>(D.ephi) + l0;
     for (int q = 0; q < P.n_q; ++q) {
-        const QDev Q = as_const(P.qs)[q];
+        const auto &Q = as_const(P.qs)[q];
         if (!Q.active) continue;
         auto mu_sel = [&](int64_t m) {
             return ldf(mpt, m) > Q.mu_pt && fabsf(ldf(meta, m)) < Q.mu_abseta &&
                    (!has_iso || ldf(miso, m) < Q.mu_iso);
         };
         auto el_sel = [&](int64_t m) { return ldf(ept, m) > Q.el_pt && fabsf(ldf(eeta, m)) < Q.el_abseta; };
-        int nmu = 0;
-        for (int64_t m = m0; m < m1; ++m) nmu += mu_sel(m) ? 1 : 0;
         // event weight: w, times the pileup lookup, times the product (left
         // to right from 1) of the selected muons' scale factors
-        float wq = w0;
+        const bool use_sf = LK && Q.sf_nb > 0;
         LkAxes ax{};
-        if (LK) {
-            ax = lk_axes(Q, edges);
-            if (Q.pu_nb > 0 && D.npu) wq = wq * lookup_bin(ax.pu, edges + Q.pu_c, D.npu[e]);
-            if (Q.sf_nb > 0) {
-                float prod = 1.0f;
-                for (int64_t m = m0; m < m1; ++m)
-                    if (mu_sel(m)) prod = prod * lookup_bin(ax.sf, edges + Q.sf_c, ldf(mpt, m));
-                wq = wq * prod;
+        if (LK) ax = lk_axes(Q, edges);
+        int nmu = 0;
+        float prod = 1.0f;
+        for (int64_t m = 0; m < nm_all; m += 64) {
+            const bool sel = m + lane < nm_all && mu_sel(m + lane);
+            uint64_t b = __ballot(sel);
+            nmu += __popcll(b);
+            if (use_sf) {
+                const float f = sel ? lookup_bin(ax.sf, edges + Q.sf_c, ldf(mpt, m + lane)) : 1.0f;
+                for (; b; b &= b - 1) prod = prod * lane_f(f, __builtin_ctzll(b));
             }
         }
+        float wq = D.w ? as_const(D.w)[e] : 1.0f;
+        if (LK && Q.pu_nb > 0 && D.npu) wq = wq * lookup_bin(ax.pu, edges + Q.pu_c, as_const(D.npu)[e]);
+        if (use_sf) wq = wq * prod;
         const bool shift = LK && Q.jes_mode == 1;
         for (int v = 0; v < Q.n_scale; ++v) {
             const float s = as_const(P.scales)[Q.scale0 + v];
             int nj = 0, nb = 0;
             float ht = 0.0f, lead = -INFINITY;
-            for (int64_t j = j0; j < j1; ++j) {
-                const float pt = ldf(jpt, j);
-                const float eta = ldf(jeta, j);
-                const float x = shift ? pt * (1.0f + s * jes_shift(ax, edges, Q.jd, pt, eta)) : pt * s;
-                if (!(x > Q.jet_pt && fabsf(eta) < Q.jet_abseta)) continue;
-                const float phi = ldf(jphi, j);
-                bool hit = false;
-                for (int64_t m = m0; m < m1 && !hit; ++m)
-                    hit = mu_sel(m) && delta_r2(eta, phi, ldf(meta, m), ldf(mphi, m)) <= Q.thr2;
-                for (int64_t m = l0; m < l1 && !hit; ++m)
-                    hit = el_sel(m) && delta_r2(eta, phi, ldf(eeta, m), ldf(ephi, m)) <= Q.thr2;
-                if (hit) continue;
-                if (nj == 0 || x > lead) lead = x;
-                ++nj;
-                ht = ht + x;
-                if (has_bt && ldf(jbt, j) > Q.btag) ++nb;
+            for (int64_t j = 0; j < nj_all; j += 64) {
+                const int64_t i = j + lane;
+                float x = 0.0f, eta = 0.0f;
+                bool sel = false;
+                if (i < nj_all) {
+                    const float pt = ldf(jpt, i);
+                    eta = ldf(jeta, i);
+                    x = shift ? pt * (1.0f + s * jes_shift(ax, edges, Q.jd, pt, eta)) : pt * s;
+                    sel = x > Q.jet_pt && fabsf(eta) < Q.jet_abseta;
+                }
+                const float phi = sel ? ldf(jphi, i) : 0.0f;
+                if (__ballot(sel) == 0) continue;
+                for (int64_t m = 0; m < nm_all; ++m)
+                    if (mu_sel(m)) sel = sel && !(delta_r2(eta, phi, ldf(meta, m), ldf(mphi, m)) <= Q.thr2);
+                for (int64_t m = 0; m < nl_all; ++m)
+                    if (el_sel(m)) sel = sel && !(delta_r2(eta, phi, ldf(eeta, m), ldf(ephi, m)) <= Q.thr2);
+                if (has_bt) nb += __popcll(__ballot(sel && ldf(jbt, sel ? i : 0) > Q.btag));
+                uint64_t b = __ballot(sel);
+                nj += __popcll(b);
+                for (; b; b &= b - 1) {
+                    const float xl = lane_f(x, __builtin_ctzll(b));
+                    ht = ht + xl;
+                    lead = fmaxf(lead, xl);
+                }
             }
             const bool pass = nmu >= Q.min_mu && nj >= Q.min_jet && (!has_bt || nb >= Q.min_b);
-            if (DBG)
-                *rec_at(P, Q.scale0 + v, D.ev0 + e) = hepk_event_record{nmu, nj, nb, pass ? 3 : 2, ht, lead, wq, 0};
-            if (pass) fill3(sink, Q, edges, v, ht, lead, nj, static_cast<double>(wq));
+            if (lane == 0) {
+                if (DBG)
+                    *rec_at(P, Q.scale0 + v, D.ev0 + e) =
+                        hepk_event_record{nmu, nj, nb, pass ? 3 : 2, ht, lead, wq, 0};
+                if (pass) fill3(sink, Q, edges, v, ht, lead, nj, static_cast<double>(wq));
+            }
         }
     }
 }
@@ -399,54 +402,67 @@ __device__ void event_direct(const PipeArgs &P, const DsDev &D, int64_t e, const
 template <int EVPL, bool EXT>
 struct Caps {
     static constexpr int TW = 64 * EVPL;             // events per wavefront tile
-    static constexpr int JK = 6 * EVPL + 1;          // jet slots per lane
-    static constexpr int MK = 2 * EVPL + 1;          // muon slots per lane
+    static constexpr int JK = 6 * EVPL;              // jet slots per lane
+    static constexpr int MK = 2 * EVPL;              // muon slots per lane
     static constexpr int EK = EXT ? 2 * EVPL : 1;    // electron slots per lane
     static constexpr int JC = 64 * JK, MC = 64 * MK, EC = 64 * EK;
-    // both lepton ranges of a jet in one word (8-bit first and count each)
-    // when the tile caps allow it
-    static constexpr bool PACK = EXT && MC <= 255 && EC <= 255;
+    // Dense candidates per pass over the tile's events (a tile with more takes
+    // its events in several passes).  The base selection lists 86 of a
+    // 64-event tile on average (99%: 123), the extended one 47 (83).
+    // (The extended schema at two events per lane runs one workgroup per CU
+    // whatever its list: it holds every jet of the tile.)
+    static constexpr int CAP = EXT ? (EVPL == 1 ? 128 : JC) : 192 * EVPL;
+    static constexpr int SW = CAP / 64;  // 64-candidate words
 };
 
-// One wavefront's LDS.  jr holds, per jet, its event's range of selected
-// muons (first | count << 16; with PACK, muons in the low and electrons in
-// the high 16 bits, first | count << 8 each) until the cone test reads it;
-// the same word then holds the jet's pt (or NaN) for the per-event walk
-// (with one scale and jet_pt >= 0: pt * s of a selected jet, else +0).
-// The selected muons and (extended schema) electrons share one pair of
-// arrays, the electrons from index EO = MC + 2 on, so one index runs over an
-// event's muons and then its electrons.
-// With several scales (MS) the cone test instead compacts the jets that can
-// be selected at some scale (the candidates) into jr, bt and jd in tile
-// order, and cpre[j] holds the number of candidates (low 16 bits) and of
-// b-tagged candidates (high 16 bits) before tile jet j; cpre shares space
-// with the compacted leptons, which are dead by then.
-template <int EVPL, bool EXT, bool LK, bool MS>
+template <bool P>
+using cpre_t = std::conditional_t<P, uint32_t, uint16_t>;
+
+// One wavefront's LDS.  The selected muons and (extended schema) electrons
+// share one pair of arrays in the content's own type, the electrons from
+// index EO = MC + 2 on, so one index runs over an event's muons and then its
+// electrons.
+template <typename T, int EVPL, bool EXT, bool LK, bool MS>
 struct WaveLds {
     using C = Caps<EVPL, EXT>;
+    // eta and phi in LDS: the content's own type in the extended schema at one
+    // event per lane (LDS is what limits its wavefronts), else float32
+    // (float16 copies would take registers beside the values of the cuts)
+    using TL = std::conditional_t<EXT && EVPL == 1, T, float>;
+    // selected muons, compacted in tile order (+2 padding), then (EXT) the
+    // selected electrons likewise from index EO
+    TL seta[C::MC + 2 + (EXT ? C::EC + 2 : 0)], sphi[C::MC + 2 + (EXT ? C::EC + 2 : 0)];
+    // jets of the events that can pass, as bits; first candidate of each
+    // such event in the dense list, as bits
+    uint64_t em[16 + C::JK];  // (JK + SW <= JK + 12 words; the second kind is read 32 lanes wide)
+    static constexpr int SM = C::JK;  // the second kind starts here
     union {
-        uint32_t rng;
-        float pt;
-    } jr[C::JC];
-    uint32_t jre[(EXT && !C::PACK) ? C::JC : 1];  // electron ranges when not packed
-    union {
+        // candidates (low 16 bits) and (EXT) b-tagged candidates (high 16
+        // bits) before tile jet j
+        cpre_t<EXT> cpre[C::JC + 1];
         struct {
-            // selected muons, compacted in tile order (+2 padding), then
-            // (EXT) the selected electrons likewise from index EO
-            float seta[C::MC + 2 + (EXT ? C::EC + 2 : 0)], sphi[C::MC + 2 + (EXT ? C::EC + 2 : 0)];
-            float ssf[LK ? C::MC + 2 : 1];  // LK: selected muons' scale factors, compacted like seta
-        };
-        uint32_t cpre[MS ? C::JC + 1 : 1];
+            // the dense candidates in tile order: pt until the cone test,
+            // then NaN for a removed one (with one scale and jet_pt >= 0:
+            // pt * s, +0 for a removed one), eta, phi, energy shift, b-tag
+            float pt[C::CAP];
+            TL eta[C::CAP], phi[C::CAP];
+            float jd[LK ? C::CAP : 1];
+            uint8_t bt[EXT ? C::CAP : 1];
+        } d;
     };
-    float jd[LK ? C::JC : 1];       // LK: each jet's energy-scale shift (jes_mode 1)
-    uint8_t bt[EXT ? C::JC : 1];
     union {
         struct {  // steps 2-3: selected leptons before lepton m
+            float ssf[LK ? C::MC : 1];  // LK: selected muons' pt, then their scale factors
             uint16_t mpre[C::MC + 1];
             uint16_t epre[EXT ? C::EC + 1 : 1];
         } p;
-        struct {  // step 5, several scales: eligible events (compacted),
-                  // jet range (first | end << 16) and weight
+        struct {  // step 4: selected-lepton ranges (first | count << 16) of the
+                  // events with candidates, muons and electrons
+            uint32_t mu[C::TW];
+            uint32_t el[EXT ? C::TW : 1];
+        } r;
+        struct {  // step 5, several scales: the listed events, candidate
+                  // range (first | end << 16) and weight
             uint32_t evjr[C::TW];
             float evw[C::TW];
         } w;
@@ -458,13 +474,13 @@ struct WaveLds {
 // several scales and LDS histograms every lane adds, zero where it does not
 // fill, at a slot of a scale no later than vlast (the query's last), so no
 // value needs its own branch.
-template <int N, bool CERT, bool LDSH, bool W2>
+template <int N, bool MS, bool LDSH, bool W2>
 __device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const FillC &F, const float *edges,
                                           const float (&xs)[N], const bool (&pass)[N / 3], int v0, double w,
                                           int vlast) {
     int sl[N];
-    find_bins<N, CERT>(F, edges, xs, sl);
-    if (CERT && LDSH) {
+    find_bins<N>(F, edges, xs, sl);
+    if (MS && LDSH) {
 #pragma unroll
         for (int n = 0; n < N; ++n)
             sink.add_if(F.base + min(v0 + n / 3, vlast) * F.per + F.off[n % 3] + sl[n], w,
@@ -480,8 +496,8 @@ __device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const 
 // (even: the fills take them two at a time).
 constexpr int kG = 4;
 
-// Walks the jets [j0, j1) of one event in order (pt of each in LDS, NaN when
-// removed by the cone or |eta| cut) for G scales at once: per scale the
+// Walks the candidates [j0, j1) of one event in order (pt of each in LDS, NaN
+// when removed by the cone test) for G scales at once: per scale the
 // left-to-right float32 H_T of the selected jets (ptv > jet_pt), their
 // count, b-tag count and maximum.  Adding only selected values keeps the sum
 // order of the definition.  ptv = pt * s, or with JM (shifted energies)
@@ -497,7 +513,7 @@ __device__ __forceinline__ void walk_jets(const WL &L, int j0, int j1, const flo
                                           float (&ht)[G], float (&lead)[G], int (&nj)[G], int (&nb)[G]) {
     float pmax = -INFINITY;
     // selected jets (low 16 bits) and selected b-tagged jets (high 16 bits)
-    // in one counter per scale: a range holds at most 64 * JK < 2^16 jets
+    // in one counter per scale: a range holds at most CAP < 2^16 jets
     uint32_t cnt[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -521,13 +537,13 @@ __device__ __forceinline__ void walk_jets(const WL &L, int j0, int j1, const flo
     };
     int k = j0;
     for (; k + 2 <= j1; k += 2) {
-        const float p0 = L.jr[k].pt, p1 = L.jr[k + 1].pt;
-        const float d0 = JM ? L.jd[k] : 0.0f, d1 = JM ? L.jd[k + 1] : 0.0f;
-        const int b0 = EXT ? L.bt[k] : 0, b1 = EXT ? L.bt[k + 1] : 0;
+        const float p0 = L.d.pt[k], p1 = L.d.pt[k + 1];
+        const float d0 = JM ? L.d.jd[k] : 0.0f, d1 = JM ? L.d.jd[k + 1] : 0.0f;
+        const int b0 = EXT ? L.d.bt[k] : 0, b1 = EXT ? L.d.bt[k + 1] : 0;
         step(p0, d0, b0);
         step(p1, d1, b1);
     }
-    if (k < j1) step(L.jr[k].pt, JM ? L.jd[k] : 0.0f, EXT ? static_cast<int>(L.bt[k]) : 0);
+    if (k < j1) step(L.d.pt[k], JM ? L.d.jd[k] : 0.0f, EXT ? static_cast<int>(L.d.bt[k]) : 0);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         nj[g] = static_cast<int>(cnt[g] & 0xffffu);
@@ -537,7 +553,7 @@ __device__ __forceinline__ void walk_jets(const WL &L, int j0, int j1, const flo
 }
 
 // The same reductions for one scale s when the cone test already stored
-// every selected jet as pt * s and every other jet as +0 (possible when
+// every selected jet as pt * s and every other candidate as +0 (possible when
 // jet_pt >= 0: a selected value exceeds jet_pt >= 0, so it is positive and
 // the count is that of positive values).  Adding +0 leaves a float32 sum of
 // positive values unchanged, so summing every stored value keeps the sum
@@ -556,12 +572,12 @@ __device__ __forceinline__ void walk_selected(const WL &L, int j0, int j1, float
     };
     int k = j0;
     for (; k + 2 <= j1; k += 2) {
-        const float x0 = L.jr[k].pt, x1 = L.jr[k + 1].pt;
-        const int b0 = EXT ? L.bt[k] : 0, b1 = EXT ? L.bt[k + 1] : 0;
+        const float x0 = L.d.pt[k], x1 = L.d.pt[k + 1];
+        const int b0 = EXT ? L.d.bt[k] : 0, b1 = EXT ? L.d.bt[k + 1] : 0;
         step(x0, b0);
         step(x1, b1);
     }
-    if (k < j1) step(L.jr[k].pt, EXT ? static_cast<int>(L.bt[k]) : 0);
+    if (k < j1) step(L.d.pt[k], EXT ? static_cast<int>(L.d.bt[k]) : 0);
     ht = h;
     nj = n;
     nb = b;
@@ -587,40 +603,75 @@ __device__ __forceinline__ TileBounds tile_bounds(const DT &D, bool has_el, int6
     return b;
 }
 
+// Number of set bits of m below this lane, plus base.
+__device__ __forceinline__ int bits_below(uint64_t m, int base) {
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+        static_cast<uint32_t>(m >> 32),
+        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), static_cast<uint32_t>(base))));
+}
+
+// The 64-bit word whose halves lanes l and l + 1 hold, in scalar registers.
+__device__ __forceinline__ uint64_t lane_u64(uint32_t x, int l) {
+    const uint32_t lo = __builtin_amdgcn_readlane(x, l), hi = __builtin_amdgcn_readlane(x, l + 1);
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
+// Inclusive prefix sum over the wavefront (every lane active).
+__device__ __forceinline__ int wave_prefix_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
+__device__ __forceinline__ void or_u64(uint64_t *p, uint64_t v) {
+    atomicOr(reinterpret_cast<unsigned long long *>(p), static_cast<unsigned long long>(v));
+}
+
 // Compacts the selected objects of a tile (sel per slot k of this lane) into
 // (eta, phi) arrays in tile order (and, with V3, a third value into o3);
-// pre[m] = number of selected objects before object m, pre[n] = total.
-template <int K, bool V3 = false>
-__device__ __forceinline__ void compact(const bool (&sel)[K], const float (&eta)[K], const float (&phi)[K], int n,
-                                        int lane, float *oeta, float *ophi, uint16_t *pre,
-                                        const float *v3 = nullptr, float *o3 = nullptr) {
+// pre[m] = number of selected objects before object m, for every m up to
+// 64 * K (all selected objects for m at or beyond the tile's count).
+// Returns the number of selected objects.
+template <int K, bool V3, typename TL>
+__device__ __forceinline__ int compact(const bool (&sel)[K], const float (&eta)[K], const float (&phi)[K],
+                                       int lane, TL *oeta, TL *ophi, uint16_t *pre, const float *v3 = nullptr,
+                                       float *o3 = nullptr) {
     int run = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int m = lane + 64 * k;
         const uint64_t bal = __ballot(sel[k]);
-        const int before = run + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                     static_cast<uint32_t>(bal >> 32),
-                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u)));
-        if (m < n) pre[m] = static_cast<uint16_t>(before);
+        const int before = bits_below(bal, run);
+        pre[lane + 64 * k] = static_cast<uint16_t>(before);
         if (sel[k]) {
-            oeta[before] = eta[k];
-            ophi[before] = phi[k];
+            oeta[before] = static_cast<TL>(eta[k]);
+            ophi[before] = static_cast<TL>(phi[k]);
             if (V3) o3[before] = v3[k];
         }
         run += __popcll(bal);
     }
-    if (lane == 0) pre[n] = static_cast<uint16_t>(run);
+    pre[64 * K] = static_cast<uint16_t>(run);
+    return run;
 }
 
 // MS: the plan has queries with several jet-energy scales (every query then
 // takes the scale-group walk of step 5; otherwise every query has one scale).
-// Occupancy targets: base schema, one scale: six wavefronts per SIMD (at most
-// 80 VGPRs), measured the best trade between latency hiding and the
-// registers that hold a tile in flight; extended schema: four (its
-// wavefronts need twice the LDS); several scales: two, which is what LDS
-// allows next to the histograms of 20 scales, so the walk and the fills
-// may use the registers for instruction-level parallelism instead.
+// What bounds it: VALU issue and, per wavefront, the wait for a tile's loads
+// and a dozen dependent LDS round trips; so the dense list (fewer
+// instructions per tile: base 545 -> 465, 20 scales 1630 -> 1340) and as many
+// wavefronts as registers and LDS allow.  The base schema at one scale gets six
+// per SIMD (at most 80 VGPRs; five took 5% longer per 1e7 events, seven, in
+// 256-thread workgroups, 24%), the others four.  Before and after the dense
+// list: 1e7 base events 210 -> 203 us, eight queries over 6.25e6 events 764 ->
+// 555 us, 20 scales over 2e7 float16 events 1031 -> 900 us, 20 shifts with
+// lookup weights over 1e7 1467 -> 783 us (there also two wavefronts per SIMD
+// -> four: the list needs 3.9 KB of LDS per wavefront where all jets took
+// 8 KB, and the shift and scale-factor searches run for listed jets and
+// selected muons only).  Loading the next tile into the registers while the
+// list is worked on was slower at four wavefronts (280 us against 240).
 // DBG: also write every event's per-scale record (counts, H_T, leading pt,
 // whether the event was walked and whether it passed) to P.rec -- the
 // intermediate values of the pass, for checking them one by one.  Product
@@ -633,8 +684,9 @@ template <typename T, bool EXT, int WAVES, int EVPL, bool LDSH, bool MS, bool DB
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(MS ? 2 : (EXT || LK ? 4 : 6)))) void
 pipeline_kernel(PipeArgs P) {
     using C = Caps<EVPL, EXT>;
-    constexpr int TW = C::TW, JK = C::JK, MK = C::MK, EK = C::EK;
-    __shared__ WaveLds<EVPL, EXT, LK, MS> wl[WAVES];
+    constexpr int TW = C::TW, JK = C::JK, MK = C::MK, EK = C::EK, CAP = C::CAP;
+    __shared__ WaveLds<T, EVPL, EXT, LK, MS> wl[WAVES];
+    using TL = typename WaveLds<T, EVPL, EXT, LK, MS>::TL;
     // per workgroup: [sumw | sumw2 (LK) | counts (u32) | edges | scales]
     extern __shared__ double dyn[];
 
@@ -681,9 +733,6 @@ pipeline_kernel(PipeArgs P) {
     const int64_t nT = chs[P.chunk_end - 1].pre + (chs[P.chunk_end - 1].t1 - chs[P.chunk_end - 1].t0) - T0;
     const int64_t my0 = T0 + nT * blockIdx.x / gridDim.x;
     const int64_t my1 = T0 + nT * (blockIdx.x + 1) / gridDim.x;
-    int qlast = -1;  // the last active query (its cone test ends a tile's use of the columns)
-    for (int q = 0; q < P.n_q; ++q)
-        if (as_const(P.qs)[q].active) qlast = q;
     int cfirst = P.chunk_begin;
     for (int hi = P.chunk_end - 1; cfirst < hi;) {  // last chunk with pre <= my0
         const int mid = (cfirst + hi + 1) >> 1;
@@ -714,11 +763,6 @@ pipeline_kernel(PipeArgs P) {
         const bool has_el = EXT && D.eoff != nullptr;
         const bool has_bt = EXT && D.jbt != nullptr;
 
-        // several scales: the next (sub-)tile's loads fly during the walks and
-        // fills (see the tile loop below) -- where the registers allow it
-        // (LDS histograms, workgroups of at most 512 threads, one event per
-        // lane: up to 256 VGPRs; the other shapes would spill)
-        constexpr bool PIPE = MS && LDSH && WAVES <= 8 && EVPL == 1;
         // The raw loads of one tile (the offsets as their low 32-bit words:
         // tile-relative differences are exact modulo 2^32).
         // (content as raw bits: float32, or float16 in the low half)
@@ -753,7 +797,7 @@ pipeline_kernel(PipeArgs P) {
         // consecutive objects).  Buffer loads over exactly the tile's range
         // of each column read 0 past its end, which is the value every
         // unused slot must hold.
-        auto issue = [&](int64_t e0, int ne, const TileBounds &b, Raw &R) {
+        auto issue = [&](int64_t e0, int ne, const TileBounds &b, Raw &R) __attribute__((always_inline)) {
             // the extended schema measured 1.5% faster with nontemporal loads,
             // the base schema 1.3% slower
             constexpr int AUX = EXT ? kBufNt : 0;
@@ -830,7 +874,7 @@ pipeline_kernel(PipeArgs P) {
         };
         // Every value of R is used here, so the compiler waits for the tile's
         // loads at this point (once), not at each value's first use.
-        auto settle = [&](Raw &R) {
+        auto settle = [&](Raw &R) __attribute__((always_inline)) {
 #pragma unroll
             for (int r = 0; r < EVPL; ++r)
                 asm volatile("" ::"v"(R.j0[r]), "v"(R.j1[r]), "v"(R.m0[r]), "v"(R.m1[r]), "v"(R.w[r]));
@@ -853,7 +897,7 @@ pipeline_kernel(PipeArgs P) {
             }
         };
         // Steps 2-5 for every query on a settled tile.
-        auto work = [&](int64_t e0, int ne, const TileBounds &B, Raw &R, auto &&after_cone) {
+        auto work = [&](int64_t e0, int ne, const TileBounds &B, Raw &R) __attribute__((always_inline)) {
             const int nj = B.nj, nm = B.nm, nl = B.nl;
             int32_t jb[EVPL], je[EVPL], mb[EVPL], me[EVPL], lb[EVPL], le[EVPL];
             float wv[EVPL];
@@ -893,72 +937,146 @@ pipeline_kernel(PipeArgs P) {
             }
             (void)jbt;
             (void)lpt;
-            for (int q = 0; q < P.n_q; ++q) {
-                // (values derived from the lane index are recomputed per
-                // query rather than held across the query loop)
+            // Per query, the events [wlo, whi) of the tile: all of them, unless
+            // they list more candidates than the dense list holds; then half as
+            // many, and the others in further passes.
+            int wlo = 0, whi = TW;
+            for (int q = 0; q < P.n_q;) {
+                // (values derived from the lane index and from the events'
+                // ranges are recomputed per query rather than held across the
+                // query loop, where they would spill)
                 asm volatile("" : "+v"(lane));
+#pragma unroll
+                for (int r = 0; r < EVPL; ++r) {
+                    asm volatile("" : "+v"(jb[r]), "+v"(je[r]), "+v"(mb[r]), "+v"(me[r]), "+v"(wv[r]));
+                    if (EXT) asm volatile("" : "+v"(lb[r]), "+v"(le[r]));
+                }
                 // the query's fields are read in place (scalar loads near their
                 // uses) rather than copied: a copy would hold ~45 SGPRs for the
                 // whole query and spill
                 const auto &Q = as_const(P.qs)[q];
-                if (!Q.active) continue;
+                if (!Q.active) {
+                    ++q;
+                    continue;
+                }
                 // the query's cut constants, read once and pinned by one
                 // statement (loads issued together, one wait; unpinned, the
                 // compiler reloads them inside the loops below, a wait each)
                 float mu_pt = Q.mu_pt, mu_abseta = Q.mu_abseta, mu_iso = Q.mu_iso;
                 float el_pt = EXT ? Q.el_pt : 0.0f, el_abseta = EXT ? Q.el_abseta : 0.0f;
-                float jet_pt = Q.jet_pt, thr2 = Q.thr2, jet_abseta = Q.jet_abseta, smax = Q.smax;
+                float jet_pt = Q.jet_pt, thr2 = Q.thr2, jet_abseta = Q.jet_abseta, smax = Q.smax, ptmin = Q.ptmin;
                 float btag = EXT ? Q.btag : 0.0f;
                 int min_mu = Q.min_mu, min_jet = Q.min_jet, min_b = has_bt ? Q.min_b : 0;
                 asm volatile(""
                              : "+s"(mu_pt), "+s"(mu_abseta), "+s"(mu_iso), "+s"(el_pt), "+s"(el_abseta),
-                               "+s"(jet_pt), "+s"(thr2), "+s"(jet_abseta), "+s"(smax), "+s"(btag), "+s"(min_mu),
-                               "+s"(min_jet), "+s"(min_b));
+                               "+s"(jet_pt), "+s"(thr2), "+s"(jet_abseta), "+s"(smax), "+s"(ptmin), "+s"(btag),
+                               "+s"(min_mu), "+s"(min_jet), "+s"(min_b));
                 // lookup corrections of this query (LK kernels): which are on,
                 // the tables as axes over the edge table
                 const bool use_pu = LK && Q.pu_nb > 0 && D.npu != nullptr;
                 const bool use_sf = LK && Q.sf_nb > 0;
                 const bool shift = LK && Q.jes_mode == 1;
-                const float smin = LK ? Q.smin : 0.0f;
                 // ---- 2. lepton selection; selected leptons compacted into LDS
                 // (all compares evaluated: no branches per slot)
                 {
                     bool sel[MK];
 #pragma unroll
                     for (int k = 0; k < MK; ++k)
-                        sel[k] = (lane + 64 * k < nm) & (mpt[k] > mu_pt) & (fabsf(meta[k]) < mu_abseta) &
+                        sel[k] = (lane + 64 * k < nm) & (mpt[k] > mu_pt) &
+                                 (fabsf(meta[k]) < mu_abseta) &
                                  (!has_iso | (miso[k] < mu_iso));
                     if (use_sf) {
-                        // each selected muon's scale factor, compacted beside it
-                        float sfv[MK];
-                        on_tables([&](const float *E) { lookup_bin_n<MK>(lk_axes(Q, E).sf, E + Q.sf_c, mpt, sel, sfv, false); });
-                        compact<MK, true>(sel, meta, mphi, nm, lane, L.seta, L.sphi, L.u.p.mpre, sfv, L.ssf);
+                        // the selected muons' pt, compacted beside them and
+                        // then replaced by their scale factors, a lane per
+                        // selected muon (one round where the slots take MK)
+                        const int ns = compact<MK, true>(sel, meta, mphi, lane, L.seta, L.sphi, L.u.p.mpre,
+                                                            mpt, L.u.p.ssf);
+                        wave_sync();
+                        on_tables([&](const float *E) {
+                            const Axis ax = lk_axes(Q, E).sf;
+                            for (int i = lane; i < ns; i += 64) {
+                                const float x[1] = {L.u.p.ssf[LK ? i : 0]};
+                                const bool use[1] = {true};
+                                float f[1];
+                                lookup_bin_n<1>(ax, E + Q.sf_c, x, use, f, false);
+                                L.u.p.ssf[LK ? i : 0] = f[0];
+                            }
+                        });
                     } else {
-                        compact<MK>(sel, meta, mphi, nm, lane, L.seta, L.sphi, L.u.p.mpre);
+                        compact<MK, false>(sel, meta, mphi, lane, L.seta, L.sphi, L.u.p.mpre);
                     }
                 }
                 if (EXT) {
                     bool sel[EK];
 #pragma unroll
                     for (int k = 0; k < EK; ++k)
-                        sel[k] = (lane + 64 * k < nl) & (lpt[k] > el_pt) & (fabsf(leta[k]) < el_abseta);
-                    compact<EK>(sel, leta, lphi, nl, lane, L.seta + (C::MC + 2), L.sphi + (C::MC + 2), L.u.p.epre);
+                        sel[k] = (lane + 64 * k < nl) & (lpt[k] > el_pt) &
+                                 (fabsf(leta[k]) < el_abseta);
+                    compact<EK, false>(sel, leta, lphi, lane, L.seta + (C::MC + 2), L.sphi + (C::MC + 2),
+                                          L.u.p.epre);
                 }
+                // ---- 3. candidate jets -- inside |eta| and, by ptmin, able to
+                // pass jet_pt at some scale -- as one mask per slot, and the
+                // number of candidates (b-tagged candidates) before every jet
+                uint64_t okm[JK];
+                {
+                    int runc = 0, runt = 0;
+#pragma unroll
+                    for (int k = 0; k < JK; ++k) {
+                        const int j = lane + 64 * k;
+                        const bool ok = (j < nj) & (fabsf(jeta[k]) < jet_abseta) &
+                                        (jpt[k] >= ptmin);
+                        okm[k] = __ballot(ok);
+                        uint32_t before = static_cast<uint32_t>(bits_below(okm[k], runc));
+                        runc += __popcll(okm[k]);
+                        if (EXT) {
+                            const uint64_t tg = __ballot(ok & has_bt & (jbt[EXT ? k : 0] > btag));
+                            before |= static_cast<uint32_t>(bits_below(tg, runt)) << 16;
+                            runt += __popcll(tg);
+                        }
+                        L.cpre[j] = static_cast<cpre_t<EXT>>(before);
+                    }
+                    L.cpre[C::JC] = static_cast<cpre_t<EXT>>(static_cast<uint32_t>(runc) |
+                                                             (EXT ? static_cast<uint32_t>(runt) << 16 : 0u));
+                }
+                if (lane < 2 * (JK + C::SW)) reinterpret_cast<uint32_t *>(L.em)[lane] = 0u;
                 wave_sync();
-                // ---- 3. each event lane writes its selected-lepton range over
-                // its jets; an event that cannot pass (too few muons, or too
-                // few jets before any cut) gets empty ranges: its jets' cone
-                // test is not needed
+                // each event's selected-lepton ranges (first | count << 16) and
+                // (below) its weight
                 int nmu[EVPL];
-                float wq[EVPL];  // the event weight of this query
+                uint32_t rmu[EVPL], rel[EVPL];
+                float wq[EVPL];
 #pragma unroll
                 for (int r = 0; r < EVPL; ++r) {
-                    nmu[r] = 0;
+                    const int s0 = L.u.p.mpre[mb[r]];
+                    nmu[r] = L.u.p.mpre[me[r]] - s0;
+                    rmu[r] = static_cast<uint32_t>(s0) | (static_cast<uint32_t>(nmu[r]) << 16);
+                    rel[r] = 0u;
+                    if (EXT) {
+                        const int u0 = L.u.p.epre[EXT ? lb[r] : 0];
+                        rel[r] = static_cast<uint32_t>(u0) |
+                                 (static_cast<uint32_t>(L.u.p.epre[EXT ? le[r] : 0] - u0) << 16);
+                    }
+                }
+                // the events that can still pass: every jet selected at any
+                // scale is a candidate, and the cone test only removes jets.
+                // Their candidates get consecutive places of the dense list.
+                // (The record kernels keep to the documented skip reasons.)
+                bool elig[EVPL];
+                int cnt[EVPL], start[EVPL];
+                int total = 0;
+                bool some = false;
+#pragma unroll
+                for (int r = 0; r < EVPL; ++r) {
+                    const uint32_t cw0 = L.cpre[jb[r]], cw1 = L.cpre[je[r]];
+                    const int nc = static_cast<int>((cw1 & 0xffffu) - (cw0 & 0xffffu));
+                    elig[r] = (lane + 64 * r < ne) & (nmu[r] >= min_mu) & (je[r] - jb[r] >= min_jet) &
+                              (lane + 64 * r >= wlo) & (lane + 64 * r < whi);
+                    if (!DBG)
+                        elig[r] = elig[r] & (nc >= min_jet) &
+                                  (!EXT | (static_cast<int>((cw1 >> 16) - (cw0 >> 16)) >= min_b));
                     wq[r] = wv[r];
-                    const int ev = lane + 64 * r;
-                    if (ev < ne) {
-                        const int s0 = L.u.p.mpre[mb[r]];
-                        nmu[r] = L.u.p.mpre[me[r]] - s0;
+                    if (LK && (DBG || elig[r])) {
                         if (use_pu)
                             on_tables([&](const float *E) {
                                 wq[r] = wq[r] * lookup_bin(lk_axes(Q, E).pu, E + Q.pu_c, R.npu[LK ? r : 0]);
@@ -966,278 +1084,251 @@ pipeline_kernel(PipeArgs P) {
                         if (use_sf) {
                             // product of the selected muons' scale factors, in order from 1
                             float prod = 1.0f;
-                            for (int i = s0; i < s0 + nmu[r]; ++i) prod = prod * L.ssf[i];
+                            const int s0 = static_cast<int>(rmu[r] & 0xffffu);
+                            for (int i = s0; i < s0 + nmu[r]; ++i) prod = prod * L.u.p.ssf[LK ? i : 0];
                             wq[r] = wq[r] * prod;
                         }
-                        const bool elig = nmu[r] >= min_mu && je[r] - jb[r] >= min_jet;
-                        constexpr int CS = C::PACK ? 8 : 16;  // count shift
-                        uint32_t pk = static_cast<uint32_t>(s0) | (static_cast<uint32_t>(elig ? nmu[r] : 0) << CS);
-                        uint32_t pke = 0;
-                        if (EXT) {
-                            const int u0 = L.u.p.epre[lb[r]];
-                            pke = static_cast<uint32_t>(u0) |
-                                  (static_cast<uint32_t>(elig ? L.u.p.epre[le[r]] - u0 : 0) << CS);
-                            if (C::PACK) pk |= pke << 16;
-                        }
-                        // two jets per step (a divergent loop: its trip count
-                        // is the largest jet count of the wavefront)
-                        int k = jb[r];
-                        for (; k + 2 <= je[r]; k += 2) {
-                            L.jr[k].rng = pk;
-                            L.jr[k + 1].rng = pk;
-                            if (EXT && !C::PACK) {
-                                L.jre[C::PACK ? 0 : k] = pke;
-                                L.jre[C::PACK ? 0 : k + 1] = pke;
+                    }
+                    cnt[r] = elig[r] ? nc : 0;
+                    const int incl = wave_prefix_sum(cnt[r]);
+                    start[r] = total + incl - cnt[r];
+                    total += __builtin_amdgcn_readlane(incl, 63);
+                    some |= elig[r];
+                    if (DBG && lane + 64 * r < min(ne, whi) && lane + 64 * r >= wlo) {
+                        // the muon count and weight of every event; the rest
+                        // only of events that are not walked (the walk writes
+                        // the other fields of walked events' records)
+                        for (int v = 0; v < Q.n_scale; ++v) {
+                            hepk_event_record *o = rec_at(P, Q.scale0 + v, D.ev0 + e0 + lane + 64 * r);
+                            o->n_mu = nmu[r];
+                            o->w = wq[r];
+                            o->reserved = 0;
+                            if (!elig[r]) {
+                                o->n_jet = 0;
+                                o->n_b = 0;
+                                o->state = 1;
+                                o->ht = 0.0f;
+                                o->lead = -INFINITY;
                             }
                         }
-                        if (k < je[r]) {
-                            L.jr[k].rng = pk;
-                            if (EXT && !C::PACK) L.jre[C::PACK ? 0 : k] = pke;
+                    }
+                    // their jets' bits
+                    if (cnt[r] > 0) {
+                        const int ja = jb[r], jz = je[r] - 1;
+                        const int wa = ja >> 6, wz = jz >> 6;
+                        const uint64_t lo = ~uint64_t(0) << (ja & 63), hi = ~uint64_t(0) >> (63 - (jz & 63));
+                        or_u64(&L.em[wa], wa == wz ? lo & hi : lo);
+                        if (wa != wz) {
+                            for (int w = wa + 1; w < wz; ++w) or_u64(&L.em[w], ~uint64_t(0));
+                            or_u64(&L.em[wz], hi);
                         }
                     }
                 }
-                wave_sync();
-                // ---- 4. cone test per jet against its event's selected
-                // leptons.  A jet outside |eta| or below jet_pt at the largest
-                // scale (with jet_pt >= 0) is selected at no scale: it skips
-                // the test and is stored as NaN.  That changes no result: a
-                // selected jet of its event has a larger pt, so the maximum
-                // and the sums and counts of selected jets are the same.
-                // With one scale and jet_pt >= 0 (zsel) this step decides the
-                // whole jet selection, so a kept jet is stored as pt * s and
-                // any other as +0, for walk_selected.
+                if (total > CAP) {
+                    // (every event has at most CAP jets, so a pass over one
+                    // event always fits)
+                    whi = wlo + (min(whi, ne) - wlo + 1) / 2;
+                    wave_sync();
+                    continue;
+                }
+                const bool any_ev = __ballot(some) != 0;
+                const bool last_pass = whi >= ne;
+                // With one scale and jet_pt >= 0 (zsel) the cone test decides
+                // the whole jet selection, so a kept jet is stored as pt * s
+                // and a removed one as +0, for walk_selected.
                 const bool zsel = !MS && jet_pt >= 0.0f;
-                // Slots in pairs (CB; three at a time spills registers): the
-                // pair's packed ranges, then the first two selected leptons of
-                // each slot's event, each set of reads in flight together (two
-                // LDS round trips per pair); only events with more leptons loop
-                // over the rest.  An event's leptons are its selected muons,
-                // then (EXT) its selected electrons: lepton i is seta[s0 + i]
-                // for i < nmu, else seta[EO + u0 + i - nmu].  A slot past the
-                // tile's jets reads a stale word: its firsts and counts are
-                // forced to 0.  Reads past a range's end land on other
-                // events' leptons or on the padding entries and are unused.
-                constexpr int CB = 2;
-                constexpr int EO = C::MC + 2;
-                // with shifted energies, every slot's shift, the searches of
-                // all slots in lockstep (their LDS reads in flight together)
-                float dsh_all[LK ? JK : 1];
-                if constexpr (LK) {
-                    if (shift)
-                        on_tables([&](const float *E) { jes_shift_n<JK>(lk_axes(Q, E), E, Q.jd, jpt, jeta, dsh_all); });
-                    else
+                if (any_ev) {
+                    // ---- 4. the lepton ranges of the events with candidates, in
+                    // order, and the first candidate of each as a bit
+                    int nrec = 0;
 #pragma unroll
-                        for (int k = 0; k < JK; ++k) dsh_all[LK ? k : 0] = 0.0f;
-                }
-                // MS: per slot, whether the jet is a candidate (selected at
-                // some scale), a b-tagged candidate, and its shift (LK)
-                bool okv[MS ? JK : 1], tagv[MS ? JK : 1];
-                float dshv[(MS && LK) ? JK : 1];
-#pragma unroll
-                for (int k = 0; k < (MS ? JK : 1); ++k) okv[k] = tagv[k] = false;
-#pragma unroll
-                for (int k0 = 0; k0 < JK; k0 += CB) {
-                    if (64 * k0 >= nj) break;  // no jet in this pair or later (uniform)
-                    // both slots' range words, then both slots' first two
-                    // leptons, each set read together and waited for once (the
-                    // pins keep the compiler from moving a read into the
-                    // per-slot code)
-                    uint32_t pk[CB], pe[CB];
-#pragma unroll
-                    for (int b = 0; b < CB; ++b) {
-                        pk[b] = pe[b] = 0u;
-                        if (k0 + b >= JK) continue;
-                        pk[b] = L.jr[lane + 64 * (k0 + b)].rng;
-                        if (EXT && !C::PACK) pe[b] = L.jre[(EXT && !C::PACK) ? lane + 64 * (k0 + b) : 0];
-                    }
-                    // (pinned in the extended schema only: the base kernel hides
-                    // the latency with more wavefronts and measured faster
-                    // with the compiler's own placement)
-                    if (EXT) asm volatile("" : "+v"(pk[0]), "+v"(pk[1]));
-                    if (EXT && !C::PACK) asm volatile("" : "+v"(pe[0]), "+v"(pe[1]));
-                    // per slot: first muon, muon count, offset of the electrons
-                    // in the lepton index, lepton count
-                    int s0[CB], nmu_[CB], ofe[CB], nlep[CB];
-                    float e0[CB], p0[CB], e1[CB], p1[CB];
-#pragma unroll
-                    for (int b = 0; b < CB; ++b) {
-                        const bool live = k0 + b < JK && lane + 64 * (k0 + b) < nj;
-                        const uint32_t wm = live ? pk[b] : 0u;
-                        const uint32_t we = live ? (C::PACK ? (pk[b] >> 16) : pe[b]) : 0u;
-                        s0[b] = static_cast<int>(C::PACK ? (wm & 0xffu) : (wm & 0xffffu));
-                        nmu_[b] = static_cast<int>(C::PACK ? ((wm >> 8) & 0xffu) : (wm >> 16));
-                        const int u0 = EXT ? static_cast<int>(C::PACK ? (we & 0xffu) : (we & 0xffffu)) : 0;
-                        const int nel = EXT ? static_cast<int>(C::PACK ? ((we >> 8) & 0xffu) : (we >> 16)) : 0;
-                        ofe[b] = EXT ? EO + u0 - nmu_[b] : s0[b];
-                        nlep[b] = nmu_[b] + nel;
-                        const int i0 = nmu_[b] >= 1 ? s0[b] : ofe[b];
-                        const int i1 = nmu_[b] >= 2 ? s0[b] + 1 : ofe[b] + 1;
-                        e0[b] = L.seta[i0];
-                        p0[b] = L.sphi[i0];
-                        e1[b] = L.seta[i1];
-                        p1[b] = L.sphi[i1];
-                    }
-                    if (EXT)
-                        asm volatile("" : "+v"(e0[0]), "+v"(p0[0]), "+v"(e1[0]), "+v"(p1[0]), "+v"(e0[1]),
-                                     "+v"(p0[1]), "+v"(e1[1]), "+v"(p1[1]));
-#pragma unroll
-                    for (int b = 0; b < CB; ++b) {
-                        const int k = k0 + b;
-                        const int j = lane + 64 * k;
-                        if (k >= JK) continue;
-                        const bool live = j < nj;
-                        // with shifted energies, the jet's shift and the largest
-                        // energy it takes over the query's scales
-                        const float dsh = shift ? dsh_all[LK ? k : 0] : 0.0f;
-                        const float ub = shift ? shifted_pt_bound(jpt[k], dsh, smin, smax) : jpt[k] * smax;
-                        const bool need = live & (fabsf(jeta[k]) < jet_abseta) & ((jet_pt < 0.0f) | (ub > jet_pt));
-                        const int cn = need ? nlep[b] : 0;
-                        bool hit = (cn >= 1 & delta_r2(jeta[k], jphi[k], e0[b], p0[b]) <= thr2) |
-                                   (cn >= 2 & delta_r2(jeta[k], jphi[k], e1[b], p1[b]) <= thr2);
-                        const int sm = s0[b], nm_ = nmu_[b], oe = ofe[b];
-                        auto lidx = [&](int i) { return i < nm_ ? sm + i : oe + i; };
-                        int i = 2;
-                        // two leptons per step: both LDS reads in flight before the math
-                        for (; i + 2 <= cn; i += 2) {
-                            const int ia = lidx(i), ib = lidx(i + 1);
-                            const float ea = L.seta[ia], pa = L.sphi[ia], eb = L.seta[ib], pb = L.sphi[ib];
-                            hit |= delta_r2(jeta[k], jphi[k], ea, pa) <= thr2;
-                            hit |= delta_r2(jeta[k], jphi[k], eb, pb) <= thr2;
+                    for (int r = 0; r < EVPL; ++r) {
+                        const bool has = cnt[r] > 0;
+                        const uint64_t b = __ballot(has);
+                        const int o = bits_below(b, nrec);
+                        if (has) {
+                            L.u.r.mu[o] = rmu[r];
+                            if (EXT) L.u.r.el[EXT ? o : 0] = rel[r];
+                            or_u64(&L.em[L.SM + (start[r] >> 6)], uint64_t(1) << (start[r] & 63));
                         }
-                        if (i < cn) {
-                            const int ia = lidx(i);
-                            hit |= delta_r2(jeta[k], jphi[k], L.seta[ia], L.sphi[ia]) <= thr2;
-                        }
-                        const bool ok = need && !hit;
-                        const bool tag = has_bt && jbt[EXT ? k : 0] > btag;
-                        if (MS) {
-                            okv[MS ? k : 0] = ok;
-                            tagv[MS ? k : 0] = ok && tag;
-                            if (LK) dshv[(MS && LK) ? k : 0] = dsh;
-                        } else if (!live) {
-                        } else if (zsel) {
-                            // one scale s (= smax): the jet's energy pt * s, or
-                            // pt * (1 + s * d) when shifted
-                            const float f = shift ? 1.0f + smax * dsh : smax;
-                            L.jr[j].pt = ok ? jpt[k] * f : 0.0f;
-                            if (EXT) L.bt[j] = (ok && tag) ? 1 : 0;
-                        } else {
-                            L.jr[j].pt = ok ? jpt[k] : __builtin_nanf("");
-                            if (LK) L.jd[LK ? j : 0] = dsh;
-                            if (EXT) L.bt[j] = tag ? 1 : 0;
-                        }
+                        nrec += __popcll(b);
                     }
-                }
-                wave_sync();
-                if (MS) {
-                    // The candidates -- jets inside |eta|, clean, and (with
-                    // jet_pt >= 0) above jet_pt at the largest energy any
-                    // scale gives them -- compacted in tile order with their
-                    // b-tag flag (and shift).  A jet that is no candidate is
-                    // selected at no scale, so walking only the candidates
-                    // adds the same values in the same order.  cpre gives
-                    // every event its candidate range and, with jet_pt >= 0,
-                    // its candidate and b-tagged candidate counts: the jets
-                    // selected and b-tagged at the largest scale.
-                    int runc = 0, runt = 0;
+                    // their candidates, in tile order
+                        int run = 0;
+                    // (the bits of all slots in one read, a 32-bit word per lane)
+                    const uint32_t ew = reinterpret_cast<const uint32_t *>(L.em)[lane & 31];
+                    const float f = (zsel && !shift) ? smax : 1.0f;
 #pragma unroll
                     for (int k = 0; k < JK; ++k) {
-                        if (64 * k >= nj) break;
-                        const int j = lane + 64 * k;
-                        const uint64_t bc = __ballot(okv[MS ? k : 0]), bg = __ballot(tagv[MS ? k : 0]);
-                        const int before = runc + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                                      static_cast<uint32_t>(bc >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bc), 0u)));
-                        const int tbefore = runt + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                                       static_cast<uint32_t>(bg >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bg), 0u)));
-                        if (j < nj) L.cpre[MS ? j : 0] = static_cast<uint32_t>(before) | (static_cast<uint32_t>(tbefore) << 16);
-                        if (okv[MS ? k : 0]) {
-                            L.jr[before].pt = jpt[k];
-                            if (EXT) L.bt[before] = tagv[MS ? k : 0] ? 1 : 0;
-                            if (LK) L.jd[LK ? before : 0] = dshv[(MS && LK) ? k : 0];
+                        const uint64_t d = okm[k] & lane_u64(ew, 2 * k);
+                        const int dst = bits_below(d, run);
+                        if (__builtin_amdgcn_inverse_ballot_w64(d)) {
+                            L.d.pt[dst] = jpt[k] * f;
+                            L.d.eta[dst] = static_cast<TL>(jeta[k]);
+                            L.d.phi[dst] = static_cast<TL>(jphi[k]);
+                            if (EXT) L.d.bt[EXT ? dst : 0] = (has_bt & (jbt[EXT ? k : 0] > btag)) ? 1 : 0;
                         }
-                        runc += __popcll(bc);
-                        runt += __popcll(bg);
+                        run += __popcll(d);
                     }
-                    if (lane == 0) L.cpre[MS ? nj : 0] = static_cast<uint32_t>(runc) | (static_cast<uint32_t>(runt) << 16);
                     wave_sync();
-                    // the tile's columns are dead from here on: the next
-                    // tile's loads can fly during this query's walk and fills
-                    if (q == qlast) after_cone();
-                }
-                // ---- 5. per-event reductions, event cut, fills
-                const FillC F = fill_consts<LDSH, MS>(Q);
-                // separate calls for the two places the edges live, so each
-                // knows its address space (no flat loads)
-                const int vlast = Q.n_scale - 1;
-                auto fill = [&](const auto &xs, const auto &pass, int v0, double w) {
-                    constexpr int N = std::extent<std::remove_reference_t<decltype(xs)>>::value;
-                    if (P.edges_in_lds)
-                        fill_bins<N, MS>(sink, F, e_s, xs, pass, v0, w, vlast);
-                    else
-                        fill_bins<N, MS>(sink, F, P.edges, xs, pass, v0, w, vlast);
-                };
-                if (!MS) {
-                    const float sc[1] = {pin<float>(as_const(P.scales)[Q.scale0])};
+                    // the cone test, a lane per candidate, CB groups of 64 at a
+                    // time (each step's LDS reads of all groups in flight
+                    // together): the candidate's event is the number of first-
+                    // candidate bits up to its own; its leptons are the
+                    // event's selected muons, then (EXT) its selected
+                    // electrons: lepton i is seta[s0 + i] for i < nmu, else
+                    // seta[EO + u0 + i - nmu].  The first two are tested
+                    // without a branch (reads past a range's end land on other
+                    // leptons or on the padding entries and are unused); only
+                    // events with more loop over the rest.
+                    constexpr int EO = C::MC + 2;
+                    const uint32_t sv = reinterpret_cast<const uint32_t *>(L.em + L.SM)[lane & 31];
+                    int ord0 = -1;  // events that start before the group, minus one
+                    auto cone = [&](auto cb, int p0) __attribute__((always_inline)) {
+                        constexpr int CB = decltype(cb)::value;
+                        uint32_t wm[CB], we[CB];
+                        float eta[CB], phi[CB], pt[CB], dsh[CB];
 #pragma unroll
-                    for (int r = 0; r < EVPL; ++r) {
-                        // an event short of muons or of jets before any cut
-                        // cannot pass: its walk is skipped
-                        const bool elig = lane + 64 * r < ne && nmu[r] >= min_mu && je[r] - jb[r] >= min_jet;
-                        float ht[1], lead[1];
-                        int njs[1], nbt[1];
-                        const int jend = elig ? je[r] : jb[r];
-                        if (zsel)
-                            walk_selected<EXT>(L, jb[r], jend, ht[0], lead[0], njs[0], nbt[0]);
-                        else if (shift)
-                            walk_jets<1, EXT, true>(L, jb[r], jend, sc, jet_pt, ht, lead, njs, nbt);
-                        else
-                            walk_jets<1, EXT, false>(L, jb[r], jend, sc, jet_pt, ht, lead, njs, nbt);
-                        const bool pass[1] = {elig && njs[0] >= min_jet && nbt[0] >= min_b};
-                        if (DBG && lane + 64 * r < ne)
-                            *rec_at(P, Q.scale0, D.ev0 + e0 + lane + 64 * r) = hepk_event_record{
-                                nmu[r], njs[0], nbt[0], elig ? (pass[0] ? 3 : 2) : 1, ht[0], lead[0], wq[r], 0};
-                        if (pass[0]) {
-                            const float xs[3] = {ht[0], lead[0], static_cast<float>(njs[0])};
-                            fill(xs, pass, 0, static_cast<double>(wq[r]));
+                        for (int b = 0; b < CB; ++b) {
+                            const uint64_t sw = lane_u64(sv, 2 * ((p0 >> 6) + b));
+                            const int o = bits_below(sw >> 1, ord0 + static_cast<int>(sw & 1u));
+                            ord0 += __popcll(sw);
+                            const int p = p0 + 64 * b + lane;
+                            wm[b] = L.u.r.mu[o];
+                            we[b] = EXT ? L.u.r.el[EXT ? o : 0] : 0u;
+                            eta[b] = ldf(L.d.eta, p);
+                            phi[b] = ldf(L.d.phi, p);
+                            pt[b] = LK ? L.d.pt[p] : 0.0f;
+                            dsh[b] = 0.0f;
                         }
-                    }
-                } else {
-                    // Several scales: the events that can pass at some scale are
-                    // compacted, and lanes take (event, group of kG scales)
-                    // pairs of them, event-major.  One walk over an event's
-                    // candidate jets serves the kG scales of its group (kG
-                    // independent chains), and a round covers a few events, so
-                    // the walks diverge little.  An event can pass only with
-                    // enough muons and enough jets before any cut (the cuts
-                    // only remove jets); with jet_pt >= 0 also only with
-                    // enough selected jets and b-tagged jets at the largest
-                    // scale: a jet selected at s <= smax is selected at smax
-                    // (rounding pt * s is monotone in s for pt >= 0, and
-                    // pt * s <= 0 <= jet_pt otherwise; with shifts, the
-                    // largest energy is at smin or smax), and those counts
-                    // are the event's candidates and b-tagged candidates.
-                    const bool prefilter = jet_pt >= 0.0f;
-                    int nel = 0;
+                        int s0[CB], nm_[CB], ofe[CB], nlep[CB];
+                        float e0[CB], f0[CB], e1[CB], f1[CB];
 #pragma unroll
-                    for (int r = 0; r < EVPL; ++r) {
-                        const uint32_t cw0 = L.cpre[MS ? jb[r] : 0], cw1 = L.cpre[MS ? je[r] : 0];
-                        const int cb = static_cast<int>(cw0 & 0xffffu), ce = static_cast<int>(cw1 & 0xffffu);
-                        bool elig = lane + 64 * r < ne && nmu[r] >= min_mu && je[r] - jb[r] >= min_jet;
-                        if (prefilter)
-                            elig = elig && ce - cb >= min_jet && static_cast<int>((cw1 >> 16) - (cw0 >> 16)) >= min_b;
-                        if (DBG && lane + 64 * r < ne) {
-                            // the muon count of every event; the rest only of
-                            // events that are not walked (the walk writes the
-                            // other fields of walked events' records)
-                            const int64_t ge = D.ev0 + e0 + lane + 64 * r;
-                            for (int v = 0; v < Q.n_scale; ++v) {
-                                hepk_event_record *o = rec_at(P, Q.scale0 + v, ge);
-                                o->n_mu = nmu[r];
-                                o->w = wq[r];
-                                o->reserved = 0;
-                                if (!elig) {
+                        for (int b = 0; b < CB; ++b) {
+                            s0[b] = static_cast<int>(wm[b] & 0xffffu);
+                            nm_[b] = static_cast<int>(wm[b] >> 16);
+                            ofe[b] = EXT ? EO + static_cast<int>(we[b] & 0xffffu) - nm_[b] : s0[b];
+                            nlep[b] = nm_[b] + static_cast<int>(we[b] >> 16);
+                            const int i0 = (!EXT || nm_[b] >= 1) ? s0[b] : ofe[b];
+                            const int i1 = (!EXT || nm_[b] >= 2) ? s0[b] + 1 : ofe[b] + 1;
+                            e0[b] = ldf(L.seta, i0);
+                            f0[b] = ldf(L.sphi, i0);
+                            e1[b] = ldf(L.seta, i1);
+                            f1[b] = ldf(L.sphi, i1);
+                        }
+                        if constexpr (LK) {
+                            if (shift)
+                                on_tables([&](const float *E) { jes_shift_n<CB>(lk_axes(Q, E), E, Q.jd, pt, eta, dsh); });
+                        }
+#pragma unroll
+                        for (int b = 0; b < CB; ++b) {
+                            const int p = p0 + 64 * b + lane;
+                            const bool live = p < total;
+                            const int cn = live ? nlep[b] : 0;
+                            bool hit = ((cn >= 1) & (delta_r2(eta[b], phi[b], e0[b], f0[b]) <= thr2)) |
+                                       ((cn >= 2) & (delta_r2(eta[b], phi[b], e1[b], f1[b]) <= thr2));
+                            const int sm = s0[b], nm2 = nm_[b], oe = ofe[b];
+                            auto lidx = [&](int i) { return (!EXT || i < nm2) ? sm + i : oe + i; };
+                            int i = 2;
+                            // two leptons per step: both LDS reads in flight before the math
+                            for (; i + 2 <= cn; i += 2) {
+                                const int ia = lidx(i), ib = lidx(i + 1);
+                                const float ea = ldf(L.seta, ia), pa = ldf(L.sphi, ia), eb = ldf(L.seta, ib),
+                                            pb = ldf(L.sphi, ib);
+                                hit |= delta_r2(eta[b], phi[b], ea, pa) <= thr2;
+                                hit |= delta_r2(eta[b], phi[b], eb, pb) <= thr2;
+                            }
+                            if (i < cn) {
+                                const int ia = lidx(i);
+                                hit |= delta_r2(eta[b], phi[b], ldf(L.seta, ia), ldf(L.sphi, ia)) <= thr2;
+                            }
+                            if (LK && shift) {
+                                if (!live) continue;
+                                if (zsel) {
+                                    // one scale s (= smax): the jet's energy pt * (1 + s * d)
+                                    const float x = pt[b] * (1.0f + smax * dsh[b]);
+                                    const bool sel = !hit & (x > jet_pt);
+                                    L.d.pt[p] = sel ? x : 0.0f;
+                                    if (EXT && !sel) L.d.bt[EXT ? p : 0] = 0;
+                                } else {
+                                    // (an energy not above jet_pt at any scale is
+                                    // removed too: the records count it so)
+                                    if (DBG && jet_pt >= 0.0f)
+                                        hit |= !(shifted_pt_bound(pt[b], dsh[b], Q.smin, smax) > jet_pt);
+                                    L.d.jd[LK ? p : 0] = dsh[b];
+                                    if (hit) L.d.pt[p] = __builtin_nanf("");
+                                }
+                            } else if (live & hit) {
+                                L.d.pt[p] = zsel ? 0.0f : __builtin_nanf("");
+                                if (EXT) L.d.bt[EXT ? p : 0] = 0;
+                            }
+                        }
+                    };
+                    for (int p0 = 0; p0 < total; p0 += 128) {
+                        if (total - p0 > 64)
+                            cone(std::integral_constant<int, 2>{}, p0);
+                        else
+                            cone(std::integral_constant<int, 1>{}, p0);
+                    }
+                    wave_sync();
+                    // ---- 5. per-event reductions, event cut, fills
+                    const FillC F = fill_consts<LDSH>(Q);
+                    // separate calls for the two places the edges live, so each
+                    // knows its address space (no flat loads)
+                    const int vlast = Q.n_scale - 1;
+                    auto fill = [&](const auto &xs, const auto &pass, int v0, double w) __attribute__((always_inline)) {
+                        constexpr int N = std::extent<std::remove_reference_t<decltype(xs)>>::value;
+                        if (P.edges_in_lds)
+                            fill_bins<N, MS>(sink, F, e_s, xs, pass, v0, w, vlast);
+                        else
+                            fill_bins<N, MS>(sink, F, P.edges, xs, pass, v0, w, vlast);
+                    };
+                    if (!MS) {
+                        const float sc[1] = {pin<float>(as_const(P.scales)[Q.scale0])};
+#pragma unroll
+                        for (int r = 0; r < EVPL; ++r) {
+                            float ht[1], lead[1];
+                            int njs[1], nbt[1];
+                            const int k0 = start[r], k1 = k0 + cnt[r];  // (empty unless elig)
+                            if (zsel)
+                                walk_selected<EXT>(L, k0, k1, ht[0], lead[0], njs[0], nbt[0]);
+                            else if (shift)
+                                walk_jets<1, EXT, true>(L, k0, k1, sc, jet_pt, ht, lead, njs, nbt);
+                            else
+                                walk_jets<1, EXT, false>(L, k0, k1, sc, jet_pt, ht, lead, njs, nbt);
+                            const bool pass[1] = {elig[r] && njs[0] >= min_jet && nbt[0] >= min_b};
+                            if (DBG && elig[r])
+                                *rec_at(P, Q.scale0, D.ev0 + e0 + lane + 64 * r) = hepk_event_record{
+                                    nmu[r], njs[0], nbt[0], pass[0] ? 3 : 2, ht[0], lead[0], wq[r], 0};
+                            if (pass[0]) {
+                                const float xs[3] = {ht[0], lead[0], static_cast<float>(njs[0])};
+                                fill(xs, pass, 0, static_cast<double>(wq[r]));
+                            }
+                        }
+                    } else {
+                        // Several scales: the events that can pass are compacted, and
+                        // lanes take (event, group of kG scales) pairs of them,
+                        // event-major.  One walk over an event's candidates
+                        // serves the kG scales of its group (kG independent
+                        // chains), and one pass of the lanes covers a few
+                        // events, so the walks diverge little.
+                        int nel = 0;
+#pragma unroll
+                        for (int r = 0; r < EVPL; ++r) {
+                            bool in = elig[r];
+                            const int k0 = start[r], k1 = k0 + cnt[r];
+                            if (DBG && jet_pt >= 0.0f && in) {
+                                // the records tell the events short of jets or
+                                // b-tagged jets at the largest scale apart
+                                int kj = 0, kb = 0;
+                                for (int k = k0; k < k1; ++k) {
+                                    const bool kept = L.d.pt[k] == L.d.pt[k];
+                                    kj += kept ? 1 : 0;
+                                    kb += (EXT && kept) ? L.d.bt[EXT ? k : 0] : 0;
+                                }
+                                in = kj >= min_jet && kb >= min_b;
+                                for (int v = 0; v < Q.n_scale && !in; ++v) {
+                                    hepk_event_record *o = rec_at(P, Q.scale0 + v, D.ev0 + e0 + lane + 64 * r);
                                     o->n_jet = 0;
                                     o->n_b = 0;
                                     o->state = 1;
@@ -1245,91 +1336,95 @@ pipeline_kernel(PipeArgs P) {
                                     o->lead = -INFINITY;
                                 }
                             }
+                            const uint64_t bal = __ballot(in);
+                            const int at = bits_below(bal, nel);
+                            if (in) {
+                                // candidate range: first in bits 0-9, end in bits
+                                // 16-25 (both at most CAP < 2^10); DBG kernels
+                                // keep the event's place in the tile in the bits
+                                // between
+                                const uint32_t ev = static_cast<uint32_t>(lane + 64 * r);
+                                L.u.w.evjr[at] = static_cast<uint32_t>(k0) | (static_cast<uint32_t>(k1) << 16) |
+                                                 (DBG ? (((ev & 63u) << 10) | ((ev >> 6) << 26)) : 0u);
+                                L.u.w.evw[at] = wq[r];
+                            }
+                            nel += __popcll(bal);
                         }
-                        const uint64_t bal = __ballot(elig);
-                        const int at = nel + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                                 static_cast<uint32_t>(bal >> 32),
-                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u)));
-                        if (elig) {
-                            // candidate range: first in bits 0-9, end in bits
-                            // 16-25 (both at most 64 * JK <= 832); DBG kernels
-                            // keep the event's place in the tile in the bits
-                            // between
-                            const uint32_t ev = static_cast<uint32_t>(lane + 64 * r);
-                            L.u.w.evjr[at] = static_cast<uint32_t>(cb) | (static_cast<uint32_t>(ce) << 16) |
-                                             (DBG ? (((ev & 63u) << 10) | ((ev >> 6) << 26)) : 0u);
-                            L.u.w.evw[at] = wq[r];
-                        }
-                        nel += __popcll(bal);
-                    }
-                    wave_sync();
-                    int V = Q.n_scale, scale0 = Q.scale0;
-                    asm volatile("" : "+s"(V), "+s"(scale0));
-                    const float *scl = (P.scales_in_lds ? s_s : P.scales) + scale0;
-                    const int NG = (V + kG - 1) / kG;
-                    const int npairs = nel * NG;
-                    int e = lane / NG, g = lane - (lane / NG) * NG;
-                    const int de = 64 / NG, dg = 64 - (64 / NG) * NG;
-                    for (int i = lane; i < npairs; i += 64) {
-                        const uint32_t jr = L.u.w.evjr[e];
-                        float sc[kG];
+                        wave_sync();
+                        int V = Q.n_scale, scale0 = Q.scale0;
+                        asm volatile("" : "+s"(V), "+s"(scale0));
+                        const float *scl = (P.scales_in_lds ? s_s : P.scales) + scale0;
+                        const int NG = (V + kG - 1) / kG;
+                        const int npairs = nel * NG;
+                        int e = lane / NG, g = lane - (lane / NG) * NG;
+                        const int de = 64 / NG, dg = 64 - (64 / NG) * NG;
+                        for (int i = lane; i < npairs; i += 64) {
+                            const uint32_t jr = L.u.w.evjr[e];
+                            float sc[kG];
 #pragma unroll
-                        for (int u = 0; u < kG; ++u) sc[u] = scl[min(g * kG + u, V - 1)];
-                        float ht[kG], lead[kG];
-                        int njs[kG], nbt[kG];
-                        const int wj0 = static_cast<int>(jr & 0x3ffu), wj1 = static_cast<int>((jr >> 16) & 0x3ffu);
-                        if (shift)
-                            walk_jets<kG, EXT, true>(L, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
-                        else
-                            walk_jets<kG, EXT, false>(L, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
-                        bool pass[kG], any = false;
-#pragma unroll
-                        for (int u = 0; u < kG; ++u) {
-                            pass[u] = g * kG + u < V && njs[u] >= min_jet && nbt[u] >= min_b;
-                            any |= pass[u];
-                        }
-                        if (DBG) {
-                            const int64_t ge = D.ev0 + e0 + (((jr >> 10) & 63u) | ((jr >> 26) << 6));
+                            for (int u = 0; u < kG; ++u) sc[u] = scl[min(g * kG + u, V - 1)];
+                            float ht[kG], lead[kG];
+                            int njs[kG], nbt[kG];
+                            const int wj0 = static_cast<int>(jr & 0x3ffu), wj1 = static_cast<int>((jr >> 16) & 0x3ffu);
+                            if (shift)
+                                walk_jets<kG, EXT, true>(L, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
+                            else
+                                walk_jets<kG, EXT, false>(L, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
+                            bool pass[kG], any = false;
 #pragma unroll
                             for (int u = 0; u < kG; ++u) {
-                                if (g * kG + u >= V) continue;
-                                hepk_event_record *o = rec_at(P, scale0 + g * kG + u, ge);
-                                o->n_jet = njs[u];
-                                o->n_b = nbt[u];
-                                o->state = pass[u] ? 3 : 2;
-                                o->ht = ht[u];
-                                o->lead = lead[u];
+                                pass[u] = g * kG + u < V && njs[u] >= min_jet && nbt[u] >= min_b;
+                                any |= pass[u];
                             }
-                        }
-                        if (any) {
-                            // FS scales' bins per search: the batch that fits the
-                            // registers of 1024-thread workgroups without spilling
-                            // (one while the next tile's loads are in flight)
-                            constexpr int FS = PIPE ? 1 : 2;
-                            const double w = static_cast<double>(L.u.w.evw[e]);
+                            if (DBG) {
+                                const int64_t ge = D.ev0 + e0 + (((jr >> 10) & 63u) | ((jr >> 26) << 6));
 #pragma unroll
-                            for (int u = 0; u < kG; u += FS) {
-                                float xs[3 * FS];
-                                bool pu[FS], anyu = false;
-#pragma unroll
-                                for (int t = 0; t < FS; ++t) {
-                                    xs[3 * t] = ht[u + t];
-                                    xs[3 * t + 1] = lead[u + t];
-                                    xs[3 * t + 2] = static_cast<float>(njs[u + t]);
-                                    pu[t] = pass[u + t];
-                                    anyu |= pu[t];
+                                for (int u = 0; u < kG; ++u) {
+                                    if (g * kG + u >= V) continue;
+                                    hepk_event_record *o = rec_at(P, scale0 + g * kG + u, ge);
+                                    o->n_jet = njs[u];
+                                    o->n_b = nbt[u];
+                                    o->state = pass[u] ? 3 : 2;
+                                    o->ht = ht[u];
+                                    o->lead = lead[u];
                                 }
-                                if (anyu) fill(xs, pu, g * kG + u, w);
                             }
-                        }
-                        e += de;
-                        g += dg;
-                        if (g >= NG) {
-                            g -= NG;
-                            e += 1;
+                            if (any) {
+                                // FS scales' bins per search: the batch that fits
+                                // the registers without spilling
+                                constexpr int FS = 2;
+                                const double w = static_cast<double>(L.u.w.evw[e]);
+#pragma unroll
+                                for (int u = 0; u < kG; u += FS) {
+                                    float xs[3 * FS];
+                                    bool pu[FS], anyu = false;
+#pragma unroll
+                                    for (int t = 0; t < FS; ++t) {
+                                        xs[3 * t] = ht[u + t];
+                                        xs[3 * t + 1] = lead[u + t];
+                                        xs[3 * t + 2] = static_cast<float>(njs[u + t]);
+                                        pu[t] = pass[u + t];
+                                        anyu |= pu[t];
+                                    }
+                                    if (anyu) fill(xs, pu, g * kG + u, w);
+                                }
+                            }
+                            e += de;
+                            g += dg;
+                            if (g >= NG) {
+                                g -= NG;
+                                e += 1;
+                            }
                         }
                     }
                 }
+                if (last_pass) {
+                    wlo = 0;
+                    ++q;
+                } else {
+                    wlo = whi;
+                }
+                whi = TW;
                 wave_sync();
             }
         };
@@ -1338,16 +1433,13 @@ pipeline_kernel(PipeArgs P) {
         // register capacity runs as consecutive sub-tiles: from its first
         // event not yet run, the event count is halved until the objects fit
         // (a few scalar loads), that sub-tile runs like a tile, and the rest
-        // of the tile follows.  Only a single event beyond the capacity goes
-        // one lane, straight from HBM.  With several scales (PIPE) the next
-        // (sub-)tile's loads are issued into R as soon as the last query's
-        // cone test is done, so they are in flight during the walks and fills.
+        // of the tile follows.  Only a single event beyond the capacity (and a
+        // tile with an event of more jets than the dense list holds) goes
+        // event by event, straight from HBM.
         int r = wave;  // this wavefront's tile (relative to c_t0)
         int eo = 0;    // events of tile r already run
         TileBounds nb{};
         if (r < nt) nb = bounds_of(r);
-        Raw R;
-        bool have = false;  // R already holds the loads of the current (sub-)tile
         while (r < nt) {
             // the lane index is re-read here so that values derived from it
             // are recomputed per tile instead of held (and spilled) across it
@@ -1373,29 +1465,24 @@ pipeline_kernel(PipeArgs P) {
                 r2 = r + WAVES;
                 eo2 = 0;
             }
-            if (oversize(B)) {
+            // an event with more jets than the dense list holds, or objects
+            // beyond the registers: event by event, straight from HBM (the
+            // tile's loads are issued all the same -- of no object when it is
+            // oversized -- so that one path defines R)
+            const bool over = oversize(B);
+            if (over) B.nj = B.nm = B.nl = 0;
+            Raw R;
+            issue(e, n, B, R);
+            settle(R);
+            bool direct = over;
+#pragma unroll
+            for (int i = 0; i < EVPL; ++i)
+                direct |= (lane + 64 * i < n) & (R.j1[i] - R.j0[i] > static_cast<uint32_t>(CAP));
+            if (__ballot(direct)) {
                 const DsDev Dc = D;
-                if (lane == 0) event_direct<T, EXT, LDSH, DBG, LK>(P, Dc, e, edges, sink);
-                have = false;
+                for (int i = 0; i < n; ++i) event_direct<T, EXT, LDSH, DBG, LK>(P, Dc, e + i, lane, edges, sink);
             } else {
-                if (!have) issue(e, n, B, R);
-                settle(R);
-                bool issued = false;
-                auto next_loads = [&]() {
-                    if (!PIPE || r2 >= nt) return;
-                    const int64_t e2 = ebase + static_cast<int64_t>(r2) * TW + eo2;
-                    int n2 = tile_events(r2) - eo2;
-                    TileBounds B2 = eo2 == 0 ? nb : tile_bounds<EXT>(D, has_el, e2, n2);
-                    while (n2 > 1 && oversize(B2)) {
-                        n2 = (n2 + 1) >> 1;
-                        B2 = tile_bounds<EXT>(D, has_el, e2, n2);
-                    }
-                    if (oversize(B2)) return;
-                    issue(e2, n2, B2, R);
-                    issued = true;
-                };
-                work(e, n, B, R, next_loads);
-                have = issued;
+                work(e, n, B, R);
             }
             r = r2;
             eo = eo2;
