@@ -1494,22 +1494,28 @@ pipeline_kernel(PipeArgs P) {
             for (int q = 0; q < P.n_q; ++q) {
                 const QDev Q = as_const(P.qs)[q];
                 if (!Q.active) continue;
-                for (int v = 0; v < Q.n_scale; ++v)
-                    for (int h = 0; h < 3; ++h) {
-                        const int ls = Q.lslot0 + v * Q.lper_scale + Q.lhoff[h];
-                        const int64_t gs = D.hist0 + Q.gslot0 + v * Q.gper_scale + Q.ghoff[h];
-                        for (int i = tid; i < Q.nbins[h] + 2; i += 64 * WAVES) {
-                            const uint32_t c = c_s[ls + i];
-                            if (c) {
-                                atomic_add_u64(&P.counts[gs + i], c);
-                                atomic_add_f64(&P.sumw[gs + i], sw_s[ls + i]);
-                                if (LK && P.sumw2) atomic_add_f64(&P.sumw2[gs + i], sw2_s[ls + i]);
-                                c_s[ls + i] = 0u;
-                                sw_s[ls + i] = 0.0;
-                                if (LK) sw2_s[ls + i] = 0.0;
-                            }
-                        }
+                // all of the query's histograms as one run of LDS slots (a loop
+                // over 60 short histograms was 60 dependent LDS round trips:
+                // 1e4 events with 20 scales 26 -> 19 us, with lookups 42 -> 33);
+                // the place in HBM from the slot's scale and observable
+                const int per = Q.lper_scale, n = per * Q.n_scale;
+                for (int i = tid; i < n; i += 64 * WAVES) {
+                    const int ls = Q.lslot0 + i;
+                    const uint32_t c = c_s[ls];
+                    if (c) {
+                        const int v = i / per, k = i - v * per;
+                        const int h = (k >= Q.lhoff[1] ? 1 : 0) + (k >= Q.lhoff[2] ? 1 : 0);
+                        const int lh = h == 0 ? Q.lhoff[0] : (h == 1 ? Q.lhoff[1] : Q.lhoff[2]);
+                        const int gh = h == 0 ? Q.ghoff[0] : (h == 1 ? Q.ghoff[1] : Q.ghoff[2]);
+                        const int64_t gs = D.hist0 + Q.gslot0 + v * Q.gper_scale + gh + (k - lh);
+                        atomic_add_u64(&P.counts[gs], c);
+                        atomic_add_f64(&P.sumw[gs], sw_s[ls]);
+                        if (LK && P.sumw2) atomic_add_f64(&P.sumw2[gs], sw2_s[ls]);
+                        c_s[ls] = 0u;
+                        sw_s[ls] = 0.0;
+                        if (LK) sw2_s[ls] = 0.0;
                     }
+                }
             }
             __syncthreads();
         }
