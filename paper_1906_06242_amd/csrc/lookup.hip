@@ -3,7 +3,7 @@
 // jet energy corrections from histogram lookups, corrections by linear
 // interpolation).  The lookup arithmetic is in lookup.hpp.
 //
-// Elementwise and HBM-bound (4 or 2 bytes read per input column and 4
+// Elementwise (4 or 2 bytes read per input column and 4
 // written per element): each thread takes four consecutive elements, read
 // with one 16-byte (float32, int32) or 8-byte (float16) load per column when
 // the arrays are aligned to that, and written with one 16-byte store.  Each
@@ -109,6 +109,67 @@ __global__ __launch_bounds__(LB) void lookup1_kernel(const X *__restrict__ x, in
     }
 }
 
+// The same with bucket tables (lookup.hpp): a count takes two LDS reads where
+// the searches take one per step, and an interpolation one 16-byte read of
+// its precomputed segment instead of eight values and a division -- random
+// LDS reads bound these kernels before (scale factors of 1.5e7 float16 muons:
+// content 27 -> 21 us, interpolation 37 -> 21 us; floor 13 us for 90 MB).
+// Contents of near-uniform edges keep the uniform-bin guess, which needs no
+// table (80 bins, 1e7 rows: 19 us against 22); edges that no key spreads keep
+// the search.
+template <typename X, int MODE, bool VEC>
+__global__ __launch_bounds__(LB) void lookup1_lut_kernel(const X *__restrict__ x, int64_t n,
+                                                         const float *__restrict__ E, int nb,
+                                                         const float *__restrict__ C, float *__restrict__ out) {
+    __shared__ float p_s[kLutMaxPoints + 2], c_s[kLutMaxPoints + 2];
+    __shared__ uint8_t l_s[kLutKeys];
+    __shared__ LutScratch w_s;
+    __shared__ Segment g_s[MODE == 1 ? kLutMaxPoints + 1 : 1];
+    // the points: edges for the slot, centres for the interpolation
+    const int np = MODE == 0 ? nb + 1 : nb;
+    for (int i = threadIdx.x; i < np; i += LB) p_s[i] = MODE == 0 ? E[i] : bin_centre(E[i], E[i + 1]);
+    stage(c_s, C, nb + 2);
+    __syncthreads();
+    if (MODE == 1)
+        for (int i = threadIdx.x; i <= nb; i += LB) g_s[MODE == 1 ? i : 0] = make_segment(p_s, c_s + 1, nb, i);
+    const float elo = as_const(E)[0], ehi = as_const(E)[nb];
+    const int64_t ng = (n + 3) >> 2;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * LB;
+    if (MODE == 0 && near_uniform(p_s, nb)) {
+        const Axis a{p_s, nb, elo, ehi, bin_inv_width(elo, ehi, nb)};
+        for (int64_t g = static_cast<int64_t>(blockIdx.x) * LB + threadIdx.x; g < ng; g += stride) {
+            float v[4], r[4];
+            load_quad<X, VEC>(x, g, n, v);
+            const bool use[4] = {true, true, true, true};
+            lookup_bin_n<4>(a, c_s, v, use, r, true);
+            store_quad<VEC>(out, g, n, r);
+        }
+        return;
+    }
+    const PointLut t = make_lut(p_s, np, l_s, w_s);
+    const float mfirst = p_s[0], mlast = p_s[np - 1];
+    for (int64_t g = static_cast<int64_t>(blockIdx.x) * LB + threadIdx.x; g < ng; g += stride) {
+        float v[4], r[4];
+        load_quad<X, VEC>(x, g, n, v);
+        if (t.M <= kLutMaxShare) {
+            int pos[4];
+            lut_count_n<4>(t, v, pos);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (MODE == 0)
+                    r[j] = (v[j] != v[j]) ? __builtin_nanf("") : c_s[pos[j]];
+                else
+                    r[j] = segment_at(g_s[pos[j]], v[j], mfirst, mlast);
+            }
+        } else {
+            const Axis a{E, nb, elo, ehi, bin_inv_width(elo, ehi, nb)};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = MODE == 0 ? lookup_bin(a, c_s, v[j]) : lookup_interp(a, c_s + 1, v[j]);
+        }
+        store_quad<VEC>(out, g, n, r);
+    }
+}
+
 // out = interpolation in pt over the |eta| row of the table D (n_eta rows of
 // n_pt values).
 template <typename X, bool LDS, bool VEC>
@@ -142,12 +203,69 @@ __global__ __launch_bounds__(LB) void jes_delta_kernel(const X *__restrict__ pt,
     }
 }
 
+// The same with bucket tables for rows and columns and precomputed segments:
+// five LDS reads per element instead of seventeen (7 rows of 24 bins, 5e7
+// float16 jets 171 -> 94 us; floor 58 us for 400 MB).
+constexpr int kMaxSegments = 1024;  // 16 KiB: still eight workgroups per CU
+
+template <typename X, bool VEC>
+__global__ __launch_bounds__(LB) void jes_lut_kernel(const X *__restrict__ pt, const X *__restrict__ eta, int64_t n,
+                                                     const float *__restrict__ EE, int ne,
+                                                     const float *__restrict__ PE, int np,
+                                                     const float *__restrict__ D, float *__restrict__ out) {
+    extern __shared__ Segment seg_s[];  // ne rows of np + 1
+    __shared__ float r_s[kLutMaxPoints + 2], p_s[kLutMaxPoints + 2];
+    __shared__ uint8_t rl_s[kLutKeys], pl_s[kLutKeys];
+    __shared__ LutScratch w_s;
+    stage(r_s, EE, ne + 1);
+    for (int i = threadIdx.x; i < np; i += LB) p_s[i] = bin_centre(PE[i], PE[i + 1]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < ne * (np + 1); i += LB) {
+        const int row = i / (np + 1);
+        seg_s[i] = make_segment(p_s, D + static_cast<int64_t>(row) * np, np, i - row * (np + 1));
+    }
+    const PointLut tr = make_lut(r_s, ne + 1, rl_s, w_s);
+    const PointLut tp = make_lut(p_s, np, pl_s, w_s);
+    const bool lut = tr.M <= kLutMaxShare && tp.M <= kLutMaxShare;
+    const float mfirst = p_s[0], mlast = p_s[np - 1];
+    const float elo = as_const(EE)[0], ehi = as_const(EE)[ne];
+    const float plo = as_const(PE)[0], phi = as_const(PE)[np];
+    const int64_t ng = (n + 3) >> 2;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * LB;
+    for (int64_t g = static_cast<int64_t>(blockIdx.x) * LB + threadIdx.x; g < ng; g += stride) {
+        float p[4], h[4], r[4];
+        load_quad<X, VEC>(pt, g, n, p);
+        load_quad<X, VEC>(eta, g, n, h);
+        if (lut) {
+            int row[4], pos[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h[j] = (h[j] != h[j]) ? -INFINITY : fabsf(h[j]);  // NaN: the first row
+            lut_count_n<4>(tr, h, row);
+            lut_count_n<4>(tp, p, pos);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                r[j] = segment_at(seg_s[(min(max(row[j], 1), ne) - 1) * (np + 1) + pos[j]], p[j], mfirst, mlast);
+        } else {
+            const Axis rows{EE, ne, elo, ehi, bin_inv_width(elo, ehi, ne)};
+            const Axis cols{PE, np, plo, phi, bin_inv_width(plo, phi, np)};
+            lookup2_n<4>(rows, cols, D, p, h, r);
+        }
+        store_quad<VEC>(out, g, n, r);
+    }
+}
+
 static bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 // Workgroups per CU, at most (a sweep of 8-64 on 5e7 rows): 16 for the
 // one-dimensional lookups, 64 for the two-dimensional shift, whose per-row
 // searches are latency-bound (911 -> 747 us against 8).
 constexpr int kLookup1WgPerCu = 16, kJesWgPerCu = 64;
+// Bucket-table kernels: eight workgroups per CU, all resident, so that each
+// builds its tables once (16 per CU: jets 103 us against 94, muons 24 against
+// 21), for inputs that give every thread of them work (2^21 rows; below, the
+// build costs what it saves) and tables that fit LDS.
+constexpr int kLutWgPerCu = 8;
+constexpr int64_t kLutMinRows = int64_t(1) << 21;
 
 static int lookup_grid(int64_t n, int per_cu) {
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(ceil_div(ceil_div(n, 4), LB), per_cu * device_cus())));
@@ -162,7 +280,11 @@ static int launch_lookup1(const void *x, int64_t n, const float *E, int nb, cons
     const X *xp = static_cast<const X *>(x);
     const int grid = lookup_grid(n, kLookup1WgPerCu);
     const size_t lb = lds ? floats * sizeof(float) : 0;
-    if (lds && vec) lookup1_kernel<X, MODE, true, true><<<grid, LB, lb, s>>>(xp, n, E, nb, C, out);
+    if (nb < kLutMaxPoints && n >= kLutMinRows) {
+        const int lg = lookup_grid(n, kLutWgPerCu);
+        if (vec) lookup1_lut_kernel<X, MODE, true><<<lg, LB, 0, s>>>(xp, n, E, nb, C, out);
+        else lookup1_lut_kernel<X, MODE, false><<<lg, LB, 0, s>>>(xp, n, E, nb, C, out);
+    } else if (lds && vec) lookup1_kernel<X, MODE, true, true><<<grid, LB, lb, s>>>(xp, n, E, nb, C, out);
     else if (lds) lookup1_kernel<X, MODE, true, false><<<grid, LB, lb, s>>>(xp, n, E, nb, C, out);
     else if (vec) lookup1_kernel<X, MODE, false, true><<<grid, LB, 0, s>>>(xp, n, E, nb, C, out);
     else lookup1_kernel<X, MODE, false, false><<<grid, LB, 0, s>>>(xp, n, E, nb, C, out);
@@ -179,7 +301,13 @@ static int launch_jes(const void *pt, const void *eta, int64_t n, const float *E
     const X *p = static_cast<const X *>(pt), *h = static_cast<const X *>(eta);
     const int grid = lookup_grid(n, kJesWgPerCu);
     const size_t lb = lds ? floats * sizeof(float) : 0;
-    if (lds && vec) jes_delta_kernel<X, true, true><<<grid, LB, lb, s>>>(p, h, n, EE, ne, PE, np, D, out);
+    const int64_t segs = static_cast<int64_t>(ne) * (np + 1);
+    if (ne < kLutMaxPoints && np <= kLutMaxPoints && segs <= kMaxSegments && n >= kLutMinRows) {
+        const int lg = lookup_grid(n, kLutWgPerCu);
+        const size_t sb = static_cast<size_t>(segs) * sizeof(Segment);
+        if (vec) jes_lut_kernel<X, true><<<lg, LB, sb, s>>>(p, h, n, EE, ne, PE, np, D, out);
+        else jes_lut_kernel<X, false><<<lg, LB, sb, s>>>(p, h, n, EE, ne, PE, np, D, out);
+    } else if (lds && vec) jes_delta_kernel<X, true, true><<<grid, LB, lb, s>>>(p, h, n, EE, ne, PE, np, D, out);
     else if (lds) jes_delta_kernel<X, true, false><<<grid, LB, lb, s>>>(p, h, n, EE, ne, PE, np, D, out);
     else if (vec) jes_delta_kernel<X, false, true><<<grid, LB, 0, s>>>(p, h, n, EE, ne, PE, np, D, out);
     else jes_delta_kernel<X, false, false><<<grid, LB, 0, s>>>(p, h, n, EE, ne, PE, np, D, out);

@@ -229,4 +229,130 @@ __device__ __forceinline__ void lookup2_n(const Axis &rows, const Axis &cols, co
     interp_at_n<N>(cols, V, x, pos, out);
 }
 
+// Number of points P[0..np) (ascending) at or below x, by a bucket table: a
+// monotone key puts every float into one of kLutKeys buckets, L[k] is the number
+// of points with a smaller key -- all of them at or below any x of bucket k --
+// and at most M points share a bucket, so M compares finish the count.  The key
+// is either linear between the first and last point or the float's own bits
+// (even steps of its logarithm), whichever spreads the points better; both are
+// monotone as computed (each operation rounds monotonically), which is all
+// the count needs.
+constexpr int kLutKeys = 256;
+constexpr int kLutMaxPoints = 255;  // counts are bytes
+constexpr int kLutMaxShare = 4;     // more compares than this: the binary search is as good
+
+struct PointLut {
+    const float *P;    // np points, then a NaN (never at or below x)
+    const uint8_t *L;  // kLutKeys entries
+    int np;
+    float lo, hi, scale;  // linear key: (x - lo) * scale
+    int shift;            // bits key (use_bits; lo >= 0): (bits(x) - bits(lo)) >> shift
+    bool use_bits;
+    int M;
+
+    __device__ __forceinline__ int key_linear(float c) const {
+        return min(static_cast<int>((c - lo) * scale), kLutKeys - 1);
+    }
+    __device__ __forceinline__ int key_bits(float c) const {
+        // (+ 0: a -0 that compares equal to lo = 0 has other bits)
+        return static_cast<int>((__builtin_bit_cast(uint32_t, c + 0.0f) - __builtin_bit_cast(uint32_t, lo)) >> shift);
+    }
+    // the bucket of x, clamped to the points' range (NaN: some bucket)
+    __device__ __forceinline__ int key(float x) const {
+        const float c = fminf(fmaxf(x, lo), hi);
+        return use_bits ? key_bits(c) : key_linear(c);
+    }
+};
+
+// Scratch of make_lut in LDS.
+struct LutScratch {
+    uint32_t share[2][kLutKeys];
+    uint32_t most[2];
+};
+
+// Builds the table (the whole workgroup; P[0..np) filled and synchronised,
+// P[np] writable, 1 <= np <= kLutMaxPoints).  M above kLutMaxShare: not suited.
+__device__ __forceinline__ PointLut make_lut(float *P, int np, uint8_t *L, LutScratch &w) {
+    PointLut t;
+    t.P = P;
+    t.L = L;
+    t.np = np;
+    t.lo = P[0] + 0.0f;  // (-0 becomes +0: its bits must not be above the others')
+    t.hi = P[np - 1];
+    const float span = t.hi - t.lo;
+    const bool linear = span > 0.0f && span < INFINITY;
+    t.scale = linear ? static_cast<float>(kLutKeys) / span : 0.0f;
+    if (!(t.scale < INFINITY)) t.scale = 0.0f;
+    const bool bits = t.lo >= 0.0f && t.hi < INFINITY;
+    const uint32_t range =
+        bits ? __builtin_bit_cast(uint32_t, t.hi) - __builtin_bit_cast(uint32_t, t.lo) : 0u;
+    t.shift = range >= static_cast<uint32_t>(kLutKeys) ? 24 - __builtin_clz(range) : 0;
+    for (int k = threadIdx.x; k < 2 * kLutKeys; k += blockDim.x) (&w.share[0][0])[k] = 0u;
+    if (threadIdx.x < 2) w.most[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) P[np] = __builtin_nanf("");
+    __syncthreads();
+    // (comparisons keep a NaN point, which valid tables do not have, in range)
+    for (int i = threadIdx.x; i < np; i += blockDim.x) {
+        const float c = fminf(fmaxf(P[i], t.lo), t.hi);
+        atomicMax(&w.most[0], atomicAdd(&w.share[0][max(t.key_linear(c), 0)], 1u) + 1u);
+        if (bits) atomicMax(&w.most[1], atomicAdd(&w.share[1][min(t.key_bits(c), kLutKeys - 1)], 1u) + 1u);
+    }
+    __syncthreads();
+    t.use_bits = bits && w.most[1] < w.most[0];
+    t.M = static_cast<int>(w.most[t.use_bits ? 1 : 0]);
+    for (int k = threadIdx.x; k < kLutKeys; k += blockDim.x) {
+        int a = 0, b = np;  // first point whose key is not below k
+        while (a < b) {
+            const int m = (a + b) >> 1;
+            if (t.key(P[m]) < k)
+                a = m + 1;
+            else
+                b = m;
+        }
+        L[k] = static_cast<uint8_t>(a);
+    }
+    __syncthreads();
+    return t;
+}
+
+// pos[n] = number of points at or below x[n] (NaN: any number up to np).
+template <int N>
+__device__ __forceinline__ void lut_count_n(const PointLut &t, const float (&x)[N], int (&pos)[N]) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) pos[n] = t.L[min(max(t.key(x[n]), 0), kLutKeys - 1)];
+    for (int m = 0; m < t.M; ++m) {
+        float e[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) e[n] = t.P[pos[n]];
+#pragma unroll
+        for (int n = 0; n < N; ++n) pos[n] += e[n] <= x[n] ? 1 : 0;
+    }
+}
+
+// One interval of an interpolation: x between centres i and i + 1 gives
+// v0 + (x - m0) * slope; before the first and after the last centre v0.  The
+// slope's division is made once per table entry: the same operands, so the
+// same bits as dividing per element.
+struct Segment {
+    float m0, v0, slope, pad;
+};
+
+// Segment i = 0..nb of the row V[0..nb) over the centres P[0..nb).
+__device__ __forceinline__ Segment make_segment(const float *P, const float *V, int nb, int i) {
+    Segment g{0.0f, V[min(max(i - 1, 0), nb - 1)], 0.0f, 0.0f};
+    if (i >= 1 && i < nb) {
+        g.m0 = P[i - 1];
+        g.slope = (V[i] - V[i - 1]) / (P[i] - P[i - 1]);
+    }
+    return g;
+}
+
+// lookup_interp of x given its segment; mfirst, mlast: the outer centres.
+__device__ __forceinline__ float segment_at(const Segment &g, float x, float mfirst, float mlast) {
+    const float d = x - g.m0;
+    const float p = d * g.slope;
+    const float r = g.v0 + p;
+    return (x != x) ? __builtin_nanf("") : ((x > mfirst && x < mlast) ? r : g.v0);
+}
+
 }  // namespace hepk
