@@ -146,8 +146,10 @@ __device__ __forceinline__ Best search(const P &X, const P &Y, const P &Z, const
 }
 
 // Triplets with first index i among n objects: C(n - i - 1, 2).
-__device__ __forceinline__ int64_t c2(int64_t m) { return m * (m - 1) / 2; }
-__device__ __forceinline__ int64_t c3(int64_t m) { return m * (m - 1) * (m - 2) / 6; }
+// (32 bits: a staged tile has at most 64 * TK = 384 objects, C(384, 3) < 2^24,
+// 384^3 < 2^26.)
+__device__ __forceinline__ int c2(int m) { return m * (m - 1) / 2; }
+__device__ __forceinline__ int c3(int m) { return static_cast<int>(static_cast<uint32_t>(m * (m - 1) * (m - 2)) / 6u); }
 
 // Mass of a triplet and its distance to the target (the arithmetic of the
 // search; NaN stays NaN).
@@ -164,7 +166,7 @@ __device__ __forceinline__ void triplet_mass(const float *X, const float *Y, con
 }
 
 // (i, j, k) of the triplet of lexicographic rank r among n objects.
-__device__ __forceinline__ void unrank(int64_t r, int n, int &i, int &j, int &k) {
+__device__ __forceinline__ void unrank(int r, int n, int &i, int &j, int &k) {
     i = 0;
     while (r >= c2(n - i - 1)) {
         r -= c2(n - i - 1);
@@ -175,14 +177,14 @@ __device__ __forceinline__ void unrank(int64_t r, int n, int &i, int &j, int &k)
         r -= n - j - 1;
         ++j;
     }
-    k = j + 1 + static_cast<int>(r);
+    k = j + 1 + r;
 }
 
 struct TripletLds {
     float x[64 * TK], y[64 * TK], z[64 * TK], e[64 * TK];  // selected objects, compacted
     uint16_t li[64 * TK];                                  // their index in the tile
     uint16_t pre[64 * TK + 1];                             // selected objects before each object
-    int64_t tp[65];                                        // triplets of the events before each
+    int32_t tp[65];                                        // triplets of the events before each
     uint64_t key[64];                                      // per event: min (d bits << 32 | rank)
     int32_t s0[64], n[64];                                 // per event: first selected, count
 };
@@ -198,24 +200,63 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
     TripletLds &L = lds[wave];
     const int64_t n_tiles = ceil_div(n_events, 64);
     const int64_t step = static_cast<int64_t>(gridDim.x) * TWV;
-    for (int64_t t = static_cast<int64_t>(blockIdx.x) * TWV + wave; t < n_tiles; t += step) {
+    // A tile's loads: both offsets of each lane's event (their low 32-bit
+    // words: tile-relative differences are exact modulo 2^32) and its objects,
+    // buffer loads over exactly the tile's ranges (0 past their ends, no
+    // per-slot branch; none for a dense tile), all in flight and waited for
+    // once.  (Issuing them while the tile before is searched gained nothing:
+    // the search is bound by VALU issue.)
+    struct Raw {
+        uint32_t o0, o1;
+        uint32_t x[TK], y[TK], z[TK], e[TK], m[TK];
+    } R;
+    auto issue = [&](int64_t e0, int64_t A, int64_t tot) __attribute__((always_inline)) {
+        const uint32_t ne1 = static_cast<uint32_t>(min<int64_t>(64, n_events - e0)) + 1u;
+        const buf_t bo = buf_span(off + e0, ne1 * 8u);
+        R.o0 = buf_u32<kBufNt>(bo, lane * 8);
+        R.o1 = buf_u32<kBufNt>(bo, lane * 8 + 8);
+        const uint32_t n = tot > 64 * TK ? 0u : static_cast<uint32_t>(tot);
+        const buf_t bx = buf_span(px + A, n * 4u), by = buf_span(py + A, n * 4u);
+        const buf_t bz = buf_span(pz + A, n * 4u), be = buf_span(en + A, n * 4u);
+        const buf_t bm = buf_span(om ? static_cast<const void *>(om + A) : static_cast<const void *>(px), om ? n : 0u);
+#pragma unroll
+        for (int k = 0; k < TK; ++k) {
+            const int i = lane + 64 * k;
+            R.x[k] = buf_u32<kBufNt>(bx, i * 4);
+            R.y[k] = buf_u32<kBufNt>(by, i * 4);
+            R.z[k] = buf_u32<kBufNt>(bz, i * 4);
+            R.e[k] = buf_u32<kBufNt>(be, i * 4);
+            R.m[k] = om ? __builtin_amdgcn_raw_buffer_load_b8(bm, i, 0, kBufNt) : 1u;
+        }
+    };
+    int64_t t = static_cast<int64_t>(blockIdx.x) * TWV + wave;
+    if (t >= n_tiles) return;
+    int64_t nA = as_const(off)[t * 64], nB = as_const(off)[min<int64_t>(t * 64 + 64, n_events)];
+    for (; t < n_tiles; t += step) {
         const int64_t e0 = t * 64;
         const int ne = static_cast<int>(min<int64_t>(64, n_events - e0));
-        const int64_t A = as_const(off)[e0];
-        const int64_t tot = as_const(off)[e0 + ne] - A;
+        const int64_t A = nA;
+        const int64_t tot = nB - nA;
+        if (t + step < n_tiles) {
+            nA = as_const(off)[(t + step) * 64];
+            nB = as_const(off)[min<int64_t>((t + step) * 64 + 64, n_events)];
+        }
         const int64_t e = e0 + lane;
         const bool act = lane < ne;
-        int64_t a0 = 0, a1 = 0;
-        if (act) {
-            a0 = off[e] - A;
-            a1 = off[e + 1] - A;
-        }
+        issue(e0, A, tot);
+        asm volatile("" ::"v"(R.o0), "v"(R.o1));
+#pragma unroll
+        for (int k = 0; k < TK; ++k)
+            asm volatile("" ::"v"(R.x[k]), "v"(R.y[k]), "v"(R.z[k]), "v"(R.e[k]), "v"(R.m[k]));
+        const int a0 = act ? static_cast<int32_t>(R.o0 - static_cast<uint32_t>(A)) : 0;
+        const int a1 = act ? static_cast<int32_t>(R.o1 - static_cast<uint32_t>(A)) : 0;
         if (tot > 64 * TK) {
             // dense tile: one lane per event from HBM
             Best b;
             if (act) {
+                const int64_t d0 = off[e] - A, d1 = off[e + 1] - A;
                 auto sel = [&](int64_t i) { return !om || om[A + i] != 0; };
-                b = search(px + A, py + A, pz + A, en + A, sel, a0, a1 - a0, target);
+                b = search(px + A, py + A, pz + A, en + A, sel, d0, d1 - d0, target);
                 out_mass[e] = b.m;
                 out_idx[3 * e] = b.i;
                 out_idx[3 * e + 1] = b.j;
@@ -223,31 +264,11 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             }
             continue;
         }
-        // 1. loads (buffer loads over exactly the tile's objects: 0 past the
-        // end, no per-slot branch, all in flight and waited for once), then
-        // the selected objects compacted in tile order
+        // 1. the selected objects compacted in tile order
         const int nobj = static_cast<int>(tot);
-        const uint32_t nb4 = static_cast<uint32_t>(nobj) * 4u;
-        const buf_t bx = buf_span(px + A, nb4), by = buf_span(py + A, nb4);
-        const buf_t bz = buf_span(pz + A, nb4), be = buf_span(en + A, nb4);
-        const buf_t bm = buf_span(om ? static_cast<const void *>(om + A) : static_cast<const void *>(px),
-                                  om ? static_cast<uint32_t>(nobj) : 0u);
-        float vx[TK], vy[TK], vz[TK], ve[TK];
-        uint32_t mk[TK];
         bool sel[TK];
 #pragma unroll
-        for (int k = 0; k < TK; ++k) {
-            const int i = lane + 64 * k;
-            vx[k] = __builtin_bit_cast(float, buf_u32<kBufNt>(bx, i * 4));
-            vy[k] = __builtin_bit_cast(float, buf_u32<kBufNt>(by, i * 4));
-            vz[k] = __builtin_bit_cast(float, buf_u32<kBufNt>(bz, i * 4));
-            ve[k] = __builtin_bit_cast(float, buf_u32<kBufNt>(be, i * 4));
-            mk[k] = om ? __builtin_amdgcn_raw_buffer_load_b8(bm, i, 0, kBufNt) : 1u;
-        }
-#pragma unroll
-        for (int k = 0; k < TK; ++k) asm volatile("" ::"v"(vx[k]), "v"(vy[k]), "v"(vz[k]), "v"(ve[k]), "v"(mk[k]));
-#pragma unroll
-        for (int k = 0; k < TK; ++k) sel[k] = (lane + 64 * k < nobj) & (mk[k] != 0u);
+        for (int k = 0; k < TK; ++k) sel[k] = (lane + 64 * k < nobj) & (R.m[k] != 0u);
         int run = 0;
 #pragma unroll
         for (int k = 0; k < TK; ++k) {
@@ -258,10 +279,10 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
                                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(bal), 0u)));
             if (i < nobj) L.pre[i] = static_cast<uint16_t>(before);
             if (sel[k]) {
-                L.x[before] = vx[k];
-                L.y[before] = vy[k];
-                L.z[before] = vz[k];
-                L.e[before] = ve[k];
+                L.x[before] = __builtin_bit_cast(float, R.x[k]);
+                L.y[before] = __builtin_bit_cast(float, R.y[k]);
+                L.z[before] = __builtin_bit_cast(float, R.z[k]);
+                L.e[before] = __builtin_bit_cast(float, R.e[k]);
                 L.li[before] = static_cast<uint16_t>(i);
             }
             run += __popcll(bal);
@@ -275,13 +296,13 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             s0 = L.pre[a0];
             nn = L.pre[a1] - s0;
         }
-        const int64_t tcount = act ? c3(nn) : 0;
-        int64_t incl = tcount;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int64_t up = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += up;
-        }
+        int incl = act ? c3(nn) : 0;
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);  // row_shr:1
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);  // row_shr:2
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);  // row_shr:4
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);  // row_shr:8
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15
+        incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);  // row_bcast:31
         L.tp[lane + 1] = incl;
         if (lane == 0) L.tp[0] = 0;
         L.s0[lane] = s0;
@@ -289,30 +310,32 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
         L.key[lane] = ~0ull;
         wave_fence_t();
         // 3-4. this lane's share of the tile's triplets
-        const int64_t T = L.tp[64];
-        const int64_t t0 = T * lane / 64, t1 = T * (lane + 1) / 64;
+        const int T = __builtin_amdgcn_readlane(incl, 63);
+        const int t0 = static_cast<int>(static_cast<uint32_t>(T) * static_cast<uint32_t>(lane) >> 6);
+        const int t1 = static_cast<int>(static_cast<uint32_t>(T) * static_cast<uint32_t>(lane + 1) >> 6);
         if (t0 < t1) {
             int ev = 0;  // the last event with tp[ev] <= t0
-            for (int lo = 0, hi = 63; lo <= hi;) {
-                const int mid = (lo + hi) >> 1;
-                if (L.tp[mid] <= t0) {
-                    ev = mid;
-                    lo = mid + 1;
-                } else {
-                    hi = mid - 1;
-                }
-            }
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) ev += L.tp[ev + d] <= t0 ? d : 0;
             while (L.tp[ev + 1] <= t0) ++ev;  // skip events without triplets
             int n = L.n[ev], base = L.s0[ev];
-            int64_t rank = t0 - L.tp[ev];
+            int rank = t0 - L.tp[ev];
             int i, j, k;
             unrank(rank, n, i, j, k);
-            uint64_t best = ~0ull;
+            // (ranks ascend, so a strict '<' keeps the first; a NaN or infinite
+            // distance is never taken)
+            float bd = INFINITY;
+            int br = 0;
+            auto merge = [&] {
+                if (bd < INFINITY)
+                    atomicMin(reinterpret_cast<unsigned long long *>(&L.key[ev]),
+                              (static_cast<unsigned long long>(__float_as_uint(bd)) << 32) | static_cast<uint32_t>(br));
+            };
             // the pair sums (X[i] + X[j]) of the current (i, j), reread only
             // when i or j moves: the same value the mass adds X[k] to
             float pxij = L.x[base + i] + L.x[base + j], pyij = L.y[base + i] + L.y[base + j];
             float pzij = L.z[base + i] + L.z[base + j], peij = L.e[base + i] + L.e[base + j];
-            for (int64_t tt = t0; tt < t1; ++tt) {
+            for (int tt = t0; tt < t1; ++tt) {
                 const float sx = pxij + L.x[base + k], sy = pyij + L.y[base + k];
                 const float sz = pzij + L.z[base + k], se = peij + L.e[base + k];
                 float m2 = se * se;
@@ -321,18 +344,17 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
                 m2 = m2 - sz * sz;
                 const float mm = (m2 < 0.0f) ? 0.0f : sqrtf(m2);
                 const float d = fabsf(mm - target);
-                if (d < INFINITY) {  // NaN and infinite distances are never taken
-                    const uint64_t key = (static_cast<uint64_t>(__float_as_uint(d)) << 32) | static_cast<uint64_t>(rank);
-                    best = key < best ? key : best;
-                }
+                const bool less = d < bd;
+                bd = less ? d : bd;
+                br = less ? rank : br;
                 // next triplet in order
                 ++rank;
                 if (++k == n) {
                     if (++j == n - 1) {
                         if (++i == n - 2) {
                             // the event is done: merge and move to the next with triplets
-                            if (best != ~0ull) atomicMin(reinterpret_cast<unsigned long long *>(&L.key[ev]), best);
-                            best = ~0ull;
+                            merge();
+                            bd = INFINITY;
                             if (tt + 1 < t1) {
                                 do {
                                     ++ev;
@@ -352,7 +374,7 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
                     peij = L.e[base + i] + L.e[base + j];
                 }
             }
-            if (best != ~0ull) atomicMin(reinterpret_cast<unsigned long long *>(&L.key[ev]), best);
+            merge();
         }
         wave_fence_t();
         // 5. each event's minimum back to its triplet and mass
@@ -362,13 +384,13 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             int32_t bi = -1, bj = -1, bk = -1;
             if (key != ~0ull) {
                 int i, j, k;
-                unrank(static_cast<int64_t>(key & 0xffffffffu), nn, i, j, k);
+                unrank(static_cast<int>(key & 0xffffffffu), nn, i, j, k);
                 float d;
                 triplet_mass(L.x + s0, L.y + s0, L.z + s0, L.e + s0, i, j, k, target, mm, d);
                 // local index = tile index of the compacted object - the event's first
-                bi = static_cast<int32_t>(L.li[s0 + i]) - static_cast<int32_t>(a0);
-                bj = static_cast<int32_t>(L.li[s0 + j]) - static_cast<int32_t>(a0);
-                bk = static_cast<int32_t>(L.li[s0 + k]) - static_cast<int32_t>(a0);
+                bi = static_cast<int32_t>(L.li[s0 + i]) - a0;
+                bj = static_cast<int32_t>(L.li[s0 + j]) - a0;
+                bk = static_cast<int32_t>(L.li[s0 + k]) - a0;
             }
             out_mass[e] = mm;
             out_idx[3 * e] = bi;
