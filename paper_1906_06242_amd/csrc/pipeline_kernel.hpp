@@ -250,32 +250,34 @@ __device__ __forceinline__ FillC fill_consts(const QT &Q) {
 // (chk), so only lanes with such a guess read edges -- rarely any lane of a
 // wavefront, so the round trip is usually skipped (eight queries, whose edges
 // stay in HBM: 588 -> 544 us per 6.25e6 events against checking every guess).
-// A binary search replaces a guess that was off.
+// A binary search replaces a guess that was off.  The fills are a third of the
+// multi-scale kernels' instructions, so no operation here is spare: without
+// the range tests that the bound makes redundant, the select chain and the
+// NaN tests 20 scales over 2e7 events took 776 us instead of 885.
 template <int N>
 __device__ __forceinline__ void find_bins(const FillC &F, const float *edges, const float (&x)[N], int (&s)[N]) {
     bool chk = false;  // some value of this lane needs the edges
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        // branch-free: the guess clamped to [0, nb - 1] before the
-        // conversion (a NaN x clamps to 0 and lands in slot 0 below), the
-        // predicates combined bitwise
+        // branch-free: the guess clamped to the bins, its bin corrected for
+        // values outside the edges (x is never NaN); a clamped or NaN guess
+        // is flagged whenever the bound flags anything
         const int h = n % 3;
         const float g = (x[n] - F.lo[h]) * F.iw[h];
-        const int gi = static_cast<int>(fminf(fmaxf(g, 0.0f), static_cast<float>(F.nb[h] - 1)));
-        const int sv = x[n] >= F.hi[h] ? F.nb[h] + 1 : gi + 1;
-        s[n] = x[n] >= F.lo[h] ? sv : 0;
-        const float f = g - static_cast<float>(gi);
-        chk |= (s[n] >= 1) & (s[n] <= F.nb[h]) &
-               (!(g < static_cast<float>(F.nb[h])) | !(g >= 0.0f) | (fabsf(f - 0.5f) >= F.ck[h]));
+        const float c = __builtin_amdgcn_fmed3f(g, 0.0f, static_cast<float>(F.nb[h] - 1));
+        s[n] = static_cast<int>(c) + 1 + (x[n] >= F.hi[h] ? 1 : 0) - (x[n] < F.lo[h] ? 1 : 0);
+        chk |= !(fabsf(__builtin_amdgcn_fractf(c) - 0.5f) < F.ck[h]);
     }
     if (chk) {
-        // every value of the lane is verified (a right guess is kept)
+        // every value of the lane by the edges (a right guess is kept)
 #pragma unroll
         for (int n = 0; n < N; ++n) {
             const int h = n % 3;
             const float *E = edges + F.eb[h];
-            if (s[n] >= 1 && s[n] <= F.nb[h] && (x[n] < E[s[n] - 1] || x[n] >= E[s[n]]))
-                s[n] = bin_search(E, F.nb[h], x[n]);
+            const int k = min(max(s[n], 1), F.nb[h]);
+            const bool in = (x[n] >= F.lo[h]) & (x[n] < F.hi[h]);
+            s[n] = x[n] >= F.hi[h] ? F.nb[h] + 1 : (in ? k : 0);
+            if (in && (x[n] < E[k - 1] || x[n] >= E[k])) s[n] = bin_search(E, F.nb[h], x[n]);
         }
     }
 }
@@ -470,10 +472,12 @@ struct WaveLds {
 };
 
 // Adds weight w to the histograms of scales v0 + n / 3 (observable n % 3)
-// of the lanes whose pass[n / 3] is set; NaN values are not filled.  With
-// several scales and LDS histograms every lane adds, zero where it does not
-// fill, at a slot of a scale no later than vlast (the query's last), so no
-// value needs its own branch.
+// of the lanes whose pass[n / 3] is set.  No value is NaN: H_T and the leading
+// pt come from selected energies, each above jet_pt and so neither NaN nor
+// -inf (with no jet selected they are 0 and -inf).  With several scales and
+// LDS histograms every lane adds, zero where it does not fill, at a slot of a
+// scale no later than vlast (the query's last), so no value needs its own
+// branch.
 template <int N, bool MS, bool LDSH, bool W2>
 __device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const FillC &F, const float *edges,
                                           const float (&xs)[N], const bool (&pass)[N / 3], int v0, double w,
@@ -484,12 +488,12 @@ __device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const 
 #pragma unroll
         for (int n = 0; n < N; ++n)
             sink.add_if(F.base + min(v0 + n / 3, vlast) * F.per + F.off[n % 3] + sl[n], w,
-                        pass[n / 3] & (xs[n] == xs[n]));
+                        pass[n / 3]);
         return;
     }
 #pragma unroll
     for (int n = 0; n < N; ++n)
-        if (pass[n / 3] && xs[n] == xs[n]) sink.add(F.base + (v0 + n / 3) * F.per + F.off[n % 3] + sl[n], w);
+        if (pass[n / 3]) sink.add(F.base + (v0 + n / 3) * F.per + F.off[n % 3] + sl[n], w);
 }
 
 // Scales per lane in the walk over an event's jets when a query has several
