@@ -250,15 +250,16 @@ struct PointLut {
     bool use_bits;
     int M;
 
-    __device__ __forceinline__ int key_linear(float c) const {
-        return min(static_cast<int>((c - lo) * scale), kLutKeys - 1);
+    __host__ __device__ __forceinline__ int key_linear(float c) const {
+        const int k = static_cast<int>((c - lo) * scale);
+        return k < kLutKeys - 1 ? k : kLutKeys - 1;
     }
-    __device__ __forceinline__ int key_bits(float c) const {
+    __host__ __device__ __forceinline__ int key_bits(float c) const {
         // (+ 0: a -0 that compares equal to lo = 0 has other bits)
         return static_cast<int>((__builtin_bit_cast(uint32_t, c + 0.0f) - __builtin_bit_cast(uint32_t, lo)) >> shift);
     }
     // the bucket of x, clamped to the points' range (NaN: some bucket)
-    __device__ __forceinline__ int key(float x) const {
+    __host__ __device__ __forceinline__ int key(float x) const {
         const float c = fminf(fmaxf(x, lo), hi);
         return use_bits ? key_bits(c) : key_linear(c);
     }
@@ -338,8 +339,8 @@ struct Segment {
 };
 
 // Segment i = 0..nb of the row V[0..nb) over the centres P[0..nb).
-__device__ __forceinline__ Segment make_segment(const float *P, const float *V, int nb, int i) {
-    Segment g{0.0f, V[min(max(i - 1, 0), nb - 1)], 0.0f, 0.0f};
+__host__ __device__ __forceinline__ Segment make_segment(const float *P, const float *V, int nb, int i) {
+    Segment g{0.0f, V[i < 1 ? 0 : i - 1], 0.0f, 0.0f};
     if (i >= 1 && i < nb) {
         g.m0 = P[i - 1];
         g.slope = (V[i] - V[i - 1]) / (P[i] - P[i - 1]);

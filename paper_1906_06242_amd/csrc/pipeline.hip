@@ -183,6 +183,7 @@ static void set_qdev(QDev &o, const hepk_query &Q, const float *const edges[3]) 
     o.active = 1;
     // lookup tables: placed by the plan (lk_place); absent until then
     o.pu_nb = o.sf_nb = o.jr_nb = o.jc_nb = 0;
+    o.jseg = -1;
     o.jes_mode = Q.jes_mode;
     for (int h = 0; h < 3; ++h) {
         const int nb = Q.nbins[h];
@@ -240,6 +241,51 @@ static int check_query(const hepk_query &Q, int i) {
 
 static int64_t hist_base(hepk_plan p, int d) { return p->shared ? 0 : d * p->ds_block; }
 
+// Appends the bucket table of the points P[0..np) to tab; false (nothing
+// appended) when there are too many or no key spreads them.
+static bool lut_place(LutDev &o, const std::vector<float> &P, std::vector<float> &tab) {
+    const int np = static_cast<int>(P.size());
+    if (np < 1 || np > kLutMaxPoints) return false;
+    PointLut t{};
+    t.np = np;
+    t.lo = P[0] + 0.0f;
+    t.hi = P[np - 1];
+    const float span = t.hi - t.lo;
+    t.scale = (span > 0.0f && std::isfinite(span)) ? static_cast<float>(kLutKeys) / span : 0.0f;
+    if (!std::isfinite(t.scale)) t.scale = 0.0f;
+    const bool bits = t.lo >= 0.0f && std::isfinite(t.hi);
+    uint32_t b0 = 0, b1 = 0;
+    std::memcpy(&b0, &t.lo, 4);
+    std::memcpy(&b1, &t.hi, 4);
+    const uint32_t range = bits ? b1 - b0 : 0u;
+    t.shift = range >= static_cast<uint32_t>(kLutKeys) ? 24 - __builtin_clz(range) : 0;
+    int best = kLutMaxShare + 1;
+    for (int mode = 0; mode < (bits ? 2 : 1); ++mode) {
+        PointLut u = t;
+        u.use_bits = mode == 1;
+        std::vector<int> share(kLutKeys, 0);
+        int most = 0;
+        for (float x : P) most = std::max(most, ++share[std::min(std::max(u.key(x), 0), kLutKeys - 1)]);
+        if (most < best) {
+            best = most;
+            t.use_bits = u.use_bits;
+        }
+    }
+    if (best > kLutMaxShare) return false;
+    o = LutDev{static_cast<int32_t>(tab.size()), 0, np, t.shift, t.use_bits ? 1 : 0, best, t.lo, t.hi, t.scale};
+    tab.insert(tab.end(), P.begin(), P.end());
+    tab.push_back(std::nanf(""));
+    o.l = static_cast<int32_t>(tab.size());
+    std::vector<uint8_t> L(kLutKeys);
+    for (int k = 0, a = 0; k < kLutKeys; ++k) {
+        while (a < np && std::min(std::max(t.key(P[a]), 0), kLutKeys - 1) < k) ++a;
+        L[k] = static_cast<uint8_t>(a);
+    }
+    tab.resize(o.l + kLutKeys / sizeof(float));
+    std::memcpy(tab.data() + o.l, L.data(), kLutKeys);
+    return true;
+}
+
 // Appends the query's lookup tables to the plan's edge table and points the
 // table entry at them.
 static void lk_place(QDev &o, const hepk_query &Q, std::vector<float> &tab) {
@@ -274,6 +320,22 @@ static void lk_place(QDev &o, const hepk_query &Q, std::vector<float> &tab) {
         o.jd = put(Q.jes_delta, static_cast<size_t>(Q.jes_n_eta) * Q.jes_n_pt);
         axis(Q.jes_eta_edges, Q.jes_n_eta, o.jr_lo, o.jr_hi, o.jr_iw);
         axis(Q.jes_pt_edges, Q.jes_n_pt, o.jc_lo, o.jc_hi, o.jc_iw);
+        // the same table as buckets and segments, where the whole edge table
+        // still goes to LDS with them
+        const int nr = Q.jes_n_eta, nc = Q.jes_n_pt;
+        std::vector<float> with = tab, centres(nc);
+        for (int i = 0; i < nc; ++i) centres[i] = bin_centre(Q.jes_pt_edges[i], Q.jes_pt_edges[i + 1]);
+        if (lut_place(o.jlr, std::vector<float>(Q.jes_eta_edges, Q.jes_eta_edges + nr + 1), with) &&
+            lut_place(o.jlc, centres, with) &&
+            (with.size() + 4 * static_cast<size_t>(nr) * (nc + 1)) * sizeof(float) <= kMaxLdsLookupBytes) {
+            o.jseg = static_cast<int32_t>(with.size());
+            for (int r = 0; r < nr; ++r)
+                for (int i = 0; i <= nc; ++i) {
+                    const Segment g = make_segment(centres.data(), Q.jes_delta + static_cast<int64_t>(r) * nc, nc, i);
+                    with.insert(with.end(), {g.m0, g.v0, g.slope, 0.0f});
+                }
+            tab.swap(with);
+        }
     }
 }
 
@@ -459,7 +521,7 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
     p->ds_block = gacc;
     p->n_slots = p->shared ? gacc : gacc * n_ds;
     p->n_edges = static_cast<int32_t>(edge_table.size());
-    p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(kMaxLdsEdgeBytes);
+    p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(p->lk ? kMaxLdsLookupBytes : kMaxLdsEdgeBytes);
     p->n_scales = static_cast<int32_t>(scales.size());
     p->scales_lds = scales.size() * sizeof(float) <= static_cast<size_t>(kMaxLdsScaleBytes);
     p->tune = t;
@@ -526,9 +588,13 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
         p->dbg_ok = fad.sharedSizeBytes == fa.sharedSizeBytes && fgd.sharedSizeBytes == fg.sharedSizeBytes;
         p->lds_max = static_cast<size_t>(mx);
         // the tables go to LDS only if they fit beside the kernel's own LDS
-        p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(kMaxLdsEdgeBytes);
+        p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(p->lk ? kMaxLdsLookupBytes : kMaxLdsEdgeBytes);
         p->scales_lds = static_cast<size_t>(p->n_scales) * sizeof(float) <= static_cast<size_t>(kMaxLdsScaleBytes);
         if (p->lds_static_glob + table_lds_bytes(p) > p->lds_max) p->edges_lds = p->scales_lds = false;
+        // (large lookup tables leave LDS to the histograms when both do not fit)
+        if (p->edges_lds && static_cast<size_t>(p->n_edges) * sizeof(float) > static_cast<size_t>(kMaxLdsEdgeBytes) &&
+            t.hist_mode == 0 && !use_lds_hist(p))
+            p->edges_lds = false;
         if (p->lds_static_glob + table_lds_bytes(p) > p->lds_max) {
             set_error("hepk_plan_create: kernel needs %zu bytes of LDS, device has %zu", p->lds_static_glob,
                       p->lds_max);

@@ -75,6 +75,19 @@ struct DsDev {
     int64_t ev0;    // events of the datasets before this one (per-event records)
 };
 
+// A bucket table (PointLut) in the plan's edge table: first point, first word
+// of the buckets, and the key's constants.
+struct LutDev {
+    int32_t p, l, np, shift, use_bits, M;
+    float lo, hi, scale;
+};
+
+template <typename LT>
+__device__ __forceinline__ PointLut lut_at(const LT &d, const float *E) {
+    return PointLut{E + d.p, reinterpret_cast<const uint8_t *>(E + d.l), d.np, d.lo, d.hi, d.scale, d.shift,
+                    d.use_bits != 0, d.M};
+}
+
 struct QDev {
     float mu_pt, mu_abseta, mu_iso, el_pt, el_abseta, jet_pt, jet_abseta, thr2, btag;
     int32_t min_mu, min_jet, min_b;
@@ -110,6 +123,10 @@ struct QDev {
     float pu_lo, pu_hi, pu_iw, sf_lo, sf_hi, sf_iw;
     float jr_lo, jr_hi, jr_iw, jc_lo, jc_hi, jc_iw;
     float smin;
+    // the shift table's bucket tables (centres of its columns, edges of its
+    // rows) and segments (rows of jc_nb + 1, 4 floats each), when jseg >= 0
+    int32_t jseg;
+    LutDev jlr, jlc;
 };
 
 struct Chunk {
@@ -193,6 +210,27 @@ template <int N>
 __device__ __forceinline__ void jes_shift_n(const LkAxes &a, const float *E, int jd, const float (&pt)[N],
                                             const float (&eta)[N], float (&out)[N]) {
     lookup2_n<N>(a.jr, a.jc, E + jd, pt, eta, out);
+}
+
+// The same from the query's bucket tables and segments (lookup.hpp: the same
+// bits with five LDS reads per jet instead of seventeen and no division:
+// lookup pass over 1e7 events 719 -> 670 us).
+template <int N, typename QT>
+__device__ __forceinline__ void jes_lut_n(const QT &Q, const float *E, const float (&pt)[N], const float (&eta)[N],
+                                          float (&out)[N]) {
+    float ae[N];
+    int row[N], pos[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) ae[n] = (eta[n] != eta[n]) ? -INFINITY : fabsf(eta[n]);  // NaN: the first row
+    lut_count_n<N>(lut_at(Q.jlr, E), ae, row);
+    lut_count_n<N>(lut_at(Q.jlc, E), pt, pos);
+    const int nr = Q.jr_nb, nc = Q.jc_nb;
+    const float mfirst = E[Q.jlc.p], mlast = E[Q.jlc.p + nc - 1];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const float *g = E + Q.jseg + 4 * ((min(max(row[n], 1), nr) - 1) * (nc + 1) + pos[n]);
+        out[n] = segment_at(Segment{g[0], g[1], g[2], 0.0f}, pt[n], mfirst, mlast);
+    }
 }
 
 // Largest pt * (1 + s * d) over the scales in [smin, smax]: the factor is
@@ -1222,7 +1260,12 @@ pipeline_kernel(PipeArgs P) {
                         }
                         if constexpr (LK) {
                             if (shift)
-                                on_tables([&](const float *E) { jes_shift_n<CB>(lk_axes(Q, E), E, Q.jd, pt, eta, dsh); });
+                                on_tables([&](const float *E) {
+                                    if (Q.jseg >= 0)
+                                        jes_lut_n<CB>(Q, E, pt, eta, dsh);
+                                    else
+                                        jes_shift_n<CB>(lk_axes(Q, E), E, Q.jd, pt, eta, dsh);
+                                });
                         }
 #pragma unroll
                         for (int b = 0; b < CB; ++b) {
@@ -1565,6 +1608,7 @@ KernelFn pick_kernel(int dtype, bool ext, int block, int evpt, bool ldsh) {
 // which the launch-configuration search weighs against atomic contention.
 constexpr int kMaxLdsHistBytes = 144 * 1024;
 constexpr int kMaxLdsEdgeBytes = 4 * 1024;
+constexpr int kMaxLdsLookupBytes = 8 * 1024;  // with lookup tables
 constexpr int kMaxLdsScaleBytes = 1024;
 
 }  // namespace hepk
