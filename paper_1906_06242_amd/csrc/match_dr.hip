@@ -273,7 +273,7 @@ __global__ __launch_bounds__(64 * MW) void match_dr_kernel(
 // says (best starts at infinity, hence `none` for an infinite cone).  Empty
 // slots are not tested (skipping their loads too gained nothing).
 // Bound by VALU issue; 5e7 float16 jets against the selected ones of 1.5e7
-// muons 158 -> 116 us (floor 70 us for 485 MB).
+// muons 158 -> 111 us (floor 70 us for 485 MB).
 template <typename T>
 __global__ __launch_bounds__(64 * MW) void match_clean_kernel(
     const int64_t *__restrict__ off_a, const T *__restrict__ eta_a, const T *__restrict__ phi_a,

@@ -709,7 +709,8 @@ __device__ __forceinline__ int compact(const bool (&sel)[K], const float (&eta)[
 // 256-thread workgroups, 24%), the others four.  Before and after the dense
 // list: 1e7 base events 210 -> 203 us, eight queries over 6.25e6 events 764 ->
 // 555 us, 20 scales over 2e7 float16 events 1031 -> 900 us, 20 shifts with
-// lookup weights over 1e7 1467 -> 783 us (there also two wavefronts per SIMD
+// lookup weights over 1e7 1467 -> 783 us (201, 523, 772 and 667 us with the
+// shorter fills, the flat merge and the bucket tables; there also two wavefronts per SIMD
 // -> four: the list needs 3.9 KB of LDS per wavefront where all jets took
 // 8 KB, and the shift and scale-factor searches run for listed jets and
 // selected muons only).  Loading the next tile into the registers while the

@@ -115,7 +115,7 @@ __device__ __forceinline__ uint32_t os_code(uint32_t m, int32_t q) { return m ==
 // LDS with their code; one lane per event walks its objects there and marks
 // the pair; then the mask bytes are written as one contiguous run.  A lane
 // per event reading its objects itself took 24 gathers of 64 scattered
-// addresses per tile and was bound by their address rate: 76 -> 29 us on
+// addresses per tile and was bound by their address rate: 76 -> 37 us on
 // 7.5e6 muons in 5e6 events (115 MB; floor 17 us).  Tiles with more objects
 // than the staging holds run in parts; a single event beyond it goes one
 // lane, straight from HBM.

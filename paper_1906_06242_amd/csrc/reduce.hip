@@ -228,7 +228,7 @@ __global__ __launch_bounds__(RB) void reduce_kernel(const int64_t *__restrict__ 
 // grows with the events so that at most kMaxSpans totals are scanned -- by
 // one workgroup in one step, each total a 64-bit load on a line of its own:
 // 5e6 events took 117 us counting included with 256-event spans (61 us of it
-// that scan), 42 us now; floor 25 us (145 MB).
+// that scan), 47 us now; floor 25 us (145 MB).
 constexpr int kMaxSpans = 4096;
 
 static int64_t span_of(int64_t n_events) {

@@ -204,7 +204,8 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
     // words: tile-relative differences are exact modulo 2^32) and its objects,
     // buffer loads over exactly the tile's ranges (0 past their ends, no
     // per-slot branch; none for a dense tile), all in flight and waited for
-    // once.  (Issuing them while the tile before is searched gained nothing:
+    // once: 175 -> 159 us on 3e6 events with the 32-bit ranks (850 VALU
+    // instructions per tile instead of 1085).  (Issuing them while the tile before is searched gained nothing:
     // the search is bound by VALU issue.)
     struct Raw {
         uint32_t o0, o1;
