@@ -47,7 +47,7 @@
 // Steps 2-5 exchange data through the wavefront's own LDS region; a
 // wavefront's LDS operations complete in issue order, so only compiler
 // ordering fences are needed between them.  A tile whose objects exceed the
-// register capacity (a 3.5-sigma fluctuation for the paper's multiplicities,
+// register capacity (a 3-sigma fluctuation of the paper's muon multiplicity,
 // always possible for arbitrary input) runs as smaller sub-tiles; a single
 // event beyond it is read straight from HBM, with the same arithmetic.
 #pragma once
@@ -442,7 +442,10 @@ __device__ __forceinline__ void event_direct(const PipeArgs &P, const DsDev &D, 
 template <int EVPL, bool EXT>
 struct Caps {
     static constexpr int TW = 64 * EVPL;             // events per wavefront tile
-    static constexpr int JK = 6 * EVPL;              // jet slots per lane
+    // (Seven jet slots where six hold the paper's five per event with 3.5 sigma
+    // to spare: at six per event six slots split most tiles, 2e6 events 68 us
+    // against 50; at five they would be 2% faster.)
+    static constexpr int JK = 6 * EVPL + 1;          // jet slots per lane
     static constexpr int MK = 2 * EVPL;              // muon slots per lane
     static constexpr int EK = EXT ? 2 * EVPL : 1;    // electron slots per lane
     static constexpr int JC = 64 * JK, MC = 64 * MK, EC = 64 * EK;
@@ -450,8 +453,8 @@ struct Caps {
     // its events in several passes).  The base selection lists 86 of a
     // 64-event tile on average (99%: 123), the extended one 47 (83).
     // (The extended schema at two events per lane runs one workgroup per CU
-    // whatever its list: it holds every jet of the tile.)
-    static constexpr int CAP = EXT ? (EVPL == 1 ? 128 : JC) : 192 * EVPL;
+    // whatever its list: it takes what 60 histograms leave of the LDS.)
+    static constexpr int CAP = EXT ? (EVPL == 1 ? 128 : 576) : 192 * EVPL;
     static constexpr int SW = CAP / 64;  // 64-candidate words
 };
 
@@ -705,11 +708,11 @@ __device__ __forceinline__ int compact(const bool (&sel)[K], const float (&eta)[
 // and a dozen dependent LDS round trips; so the dense list (fewer
 // instructions per tile: base 545 -> 465, 20 scales 1630 -> 1340) and as many
 // wavefronts as registers and LDS allow.  The base schema at one scale gets six
-// per SIMD (at most 80 VGPRs; five took 5% longer per 1e7 events, seven, in
-// 256-thread workgroups, 24%), the others four.  Before and after the dense
+// per SIMD (at most 80 VGPRs; five took 5% longer per 1e7 events, seven, which
+// 256-thread workgroups would get, 24%), the others four.  Before and after the dense
 // list: 1e7 base events 210 -> 203 us, eight queries over 6.25e6 events 764 ->
 // 555 us, 20 scales over 2e7 float16 events 1031 -> 900 us, 20 shifts with
-// lookup weights over 1e7 1467 -> 783 us (201, 523, 772 and 667 us with the
+// lookup weights over 1e7 1467 -> 783 us (203, 538, 799 and 680 us with the
 // shorter fills, the flat merge and the bucket tables; there also two wavefronts per SIMD
 // -> four: the list needs 3.9 KB of LDS per wavefront where all jets took
 // 8 KB, and the shift and scale-factor searches run for listed jets and

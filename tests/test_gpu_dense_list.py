@@ -55,13 +55,13 @@ def build(seed, jets, muons, ext, dtype):
 def shapes(name, n=1500):
     rng = np.random.default_rng(3)
     jets, muons = rng.poisson(5.0, n), rng.poisson(1.5, n)
-    if name == "full tiles":      # 384 jets and 128 muons in every 64 events
-        jets[:], muons[:] = 6, 2
-    elif name == "one beyond":    # 385 jets: every tile in two
-        jets[:], muons[:] = 6, 2
-        jets[::64] = 7
+    if name == "full tiles":      # 448 jets and 128 muons in every 64 events
+        jets[:], muons[:] = 7, 2
+    elif name == "one beyond":    # 449 jets: every tile in two
+        jets[:], muons[:] = 7, 2
+        jets[::64] = 8
     elif name == "long events":   # at and beyond the list's bound of one event
-        for i, k in enumerate((127, 128, 129, 191, 192, 193, 383, 384, 385, 1000)):
+        for i, k in enumerate((127, 128, 129, 191, 192, 193, 447, 448, 449, 1000)):
             jets[100 * i + 50], muons[100 * i + 50] = k, 2 + i
     elif name == "few":           # tiles without any event that can pass
         muons[64:1200] = 0
