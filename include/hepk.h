@@ -95,7 +95,9 @@ typedef enum hepk_reduce_op {
  *          int64[N+1]): 0 followed by the running sum of out (the offsets of
  *          the selected sub-collection; the scan stages its partial sums in
  *          offsets_out itself, so no temporary is allocated).  content may
- *          be NULL.
+ *          be NULL.  offsets_out may overlap offsets or be the same array
+ *          (the selection's offsets then replace the collection's) and may
+ *          overlap evt_mask; it must not overlap obj_mask or out.
  *   SUM    out float32[N]: left-to-right float32 sum from 0.0f, in object
  *          order -- the order of Listing 1's inner loop, kept exactly.
  *   MAX/MIN out float32[N]: extremum (-inf/+inf when empty); out_arg

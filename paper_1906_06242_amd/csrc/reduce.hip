@@ -229,7 +229,29 @@ __global__ __launch_bounds__(RB) void reduce_kernel(const int64_t *__restrict__ 
 // one workgroup in one step, each total a 64-bit load on a line of its own:
 // 5e6 events took 117 us counting included with 256-event spans (61 us of it
 // that scan), 47 us now; floor 25 us (145 MB).
+//
+// Where offsets_out overlaps offsets (a collection's offsets replaced by its
+// selection's), no total may be written while another workgroup still reads
+// its ranges: the counts are made by a launch of their own and the totals from
+// them by span_sums_kernel.
 constexpr int kMaxSpans = 4096;
+
+__global__ __launch_bounds__(RB) void span_sums_kernel(const int32_t *counts, int64_t n_events, int64_t *offsets_out,
+                                                       int64_t span) {
+    __shared__ int64_t tot_s[RW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t e1 = min<int64_t>((blockIdx.x + 1) * span, n_events);
+    int64_t sum = 0;
+    for (int64_t e = blockIdx.x * span + threadIdx.x; e < e1; e += RB) sum += counts[e];
+    sum = wave_scan(sum);
+    if (lane == 63) tot_s[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int64_t s = 0;
+        for (int w = 0; w < RW; ++w) s += tot_s[w];
+        offsets_out[e1] = s;
+    }
+}
 
 static int64_t span_of(int64_t n_events) {
     int64_t s = RB;
@@ -334,15 +356,29 @@ static int launch_reduce(const int64_t *off, int64_t n, const void *content, con
     return check_launch("hepk_reduce");
 }
 
-// COUNT with offsets_out (three launches, no temporary).
+// Whether the byte ranges [p, p + np) and [q, q + nq) share a byte.
+static bool overlap(const void *p, int64_t np, const void *q, int64_t nq) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + static_cast<uintptr_t>(nq) && b < a + static_cast<uintptr_t>(np);
+}
+
+// COUNT with offsets_out (three launches, four when it overlaps an input; no
+// temporary).
 static int launch_count_offsets(const int64_t *off, int64_t n, const uint8_t *om, const uint8_t *em, int32_t *counts,
                                 int64_t *offsets_out, hipStream_t stream) {
     const int64_t span = span_of(n);
     const int g = static_cast<int>(std::max<int64_t>(1, ceil_div(n, span)));
-    if (n > 0) {
+    const int64_t bytes = (n + 1) * static_cast<int64_t>(sizeof(int64_t));
+    if (n > 0 && (overlap(offsets_out, bytes, off, bytes) || (em && overlap(offsets_out, bytes, em, n)))) {
+        if (int rc = launch_reduce<float, R_COUNT>(off, n, nullptr, om, em, counts, nullptr, 0, stream)) return rc;
+        span_sums_kernel<<<g, RB, 0, stream>>>(counts, n, offsets_out, span);
+        if (int rc = check_launch("hepk_reduce span sums")) return rc;
+    } else if (n > 0) {
         reduce_kernel<float, R_COUNT, true><<<g, RB, 0, stream>>>(off, n, nullptr, om, em, counts, nullptr, 0, span,
                                                                   offsets_out);
         if (int rc = check_launch("hepk_reduce count")) return rc;
+    }
+    if (n > 0) {
         scan_spans_kernel<<<1, 1024, 0, stream>>>(offsets_out, n, span);
         if (int rc = check_launch("hepk_reduce scan")) return rc;
     }
