@@ -298,8 +298,8 @@ __device__ __forceinline__ void find_bins(const FillC &F, const float *edges, co
 #pragma unroll
     for (int n = 0; n < N; ++n) {
         // branch-free: the guess clamped to the bins, its bin corrected for
-        // values outside the edges (x is never NaN); a clamped or NaN guess
-        // is flagged whenever the bound flags anything
+        // values outside the edges (the slot of a NaN x is not used); a clamped
+        // or NaN guess is flagged whenever the bound flags anything
         const int h = n % 3;
         const float g = (x[n] - F.lo[h]) * F.iw[h];
         const float c = __builtin_amdgcn_fmed3f(g, 0.0f, static_cast<float>(F.nb[h] - 1));
@@ -512,13 +512,17 @@ struct WaveLds {
     } u;
 };
 
+// A selected energy is above jet_pt, so neither NaN nor -inf, and the leading
+// pt and the count are never NaN.  H_T is NaN only if negative energies sum to
+// -inf and one of +inf follows; an event's fewer than 2^32 jets above a jet_pt
+// of -1e28 do not get there.
+__device__ __forceinline__ bool ht_can_be_nan(float jet_pt) { return jet_pt < -1e28f; }
+
 // Adds weight w to the histograms of scales v0 + n / 3 (observable n % 3)
-// of the lanes whose pass[n / 3] is set.  No value is NaN: H_T and the leading
-// pt come from selected energies, each above jet_pt and so neither NaN nor
-// -inf (with no jet selected they are 0 and -inf).  With several scales and
-// LDS histograms every lane adds, zero where it does not fill, at a slot of a
-// scale no later than vlast (the query's last), so no value needs its own
-// branch.
+// of the lanes whose pass[n / 3] is set.  No value is NaN (ht_can_be_nan).  With
+// several scales and LDS histograms every lane adds, zero where it does not
+// fill, at a slot of a scale no later than vlast (the query's last), so no
+// value needs its own branch.
 template <int N, bool MS, bool LDSH, bool W2>
 __device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const FillC &F, const float *edges,
                                           const float (&xs)[N], const bool (&pass)[N / 3], int v0, double w,
@@ -1323,6 +1327,33 @@ pipeline_kernel(PipeArgs P) {
                     }
                     wave_sync();
                     // ---- 5. per-event reductions, event cut, fills
+                    if (ht_can_be_nan(jet_pt)) {
+                        // a lane per event, scale by scale, fills that test for
+                        // NaN (tests in the fills below cost 20 scales 4%); an
+                        // index of its own, so the fields are not held here
+                        // for the fills below
+                        int qn = q;
+                        asm volatile("" : "+s"(qn));
+                        const auto &N = as_const(P.qs)[qn];
+#pragma unroll
+                        for (int r = 0; r < EVPL; ++r) {
+                            if (!elig[r]) continue;
+                            for (int v = 0; v < N.n_scale; ++v) {
+                                const float sc[1] = {as_const(P.scales)[N.scale0 + v]};
+                                float ht[1], lead[1];
+                                int njs[1], nbt[1];
+                                if (shift)
+                                    walk_jets<1, EXT, true>(L, start[r], start[r] + cnt[r], sc, jet_pt, ht, lead, njs, nbt);
+                                else
+                                    walk_jets<1, EXT, false>(L, start[r], start[r] + cnt[r], sc, jet_pt, ht, lead, njs, nbt);
+                                const bool pass = njs[0] >= min_jet && nbt[0] >= min_b;
+                                if (DBG)
+                                    *rec_at(P, N.scale0 + v, D.ev0 + e0 + lane + 64 * r) = hepk_event_record{
+                                        nmu[r], njs[0], nbt[0], pass ? 3 : 2, ht[0], lead[0], wq[r], 0};
+                                if (pass) fill3(sink, N, P.edges, v, ht[0], lead[0], njs[0], static_cast<double>(wq[r]));
+                            }
+                        }
+                    }
                     const FillC F = fill_consts<LDSH>(Q);
                     // separate calls for the two places the edges live, so each
                     // knows its address space (no flat loads)
@@ -1334,7 +1365,9 @@ pipeline_kernel(PipeArgs P) {
                         else
                             fill_bins<N, MS>(sink, F, P.edges, xs, pass, v0, w, vlast);
                     };
-                    if (!MS) {
+                    if (ht_can_be_nan(jet_pt)) {
+                        // (filled above)
+                    } else if (!MS) {
                         const float sc[1] = {pin<float>(as_const(P.scales)[Q.scale0])};
 #pragma unroll
                         for (int r = 0; r < EVPL; ++r) {
