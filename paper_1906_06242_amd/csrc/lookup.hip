@@ -159,7 +159,7 @@ __global__ __launch_bounds__(LB) void lookup1_lut_kernel(const X *__restrict__ x
                 if constexpr (MODE == 0)
                     r[j] = (v[j] != v[j]) ? __builtin_nanf("") : c_s[pos[j]];
                 else
-                    r[j] = segment_at(g_s[pos[j]], v[j], mfirst, mlast);
+                    r[j] = segment_at(g_s[segment_of(pos[j], v[j], mfirst)], v[j], mfirst, mlast);
             }
         } else {
             const Axis a{E, nb, elo, ehi, bin_inv_width(elo, ehi, nb)};
@@ -244,7 +244,8 @@ __global__ __launch_bounds__(LB) void jes_lut_kernel(const X *__restrict__ pt, c
             lut_count_n<4>(tp, p, pos);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                r[j] = segment_at(seg_s[(min(max(row[j], 1), ne) - 1) * (np + 1) + pos[j]], p[j], mfirst, mlast);
+                r[j] = segment_at(seg_s[(min(max(row[j], 1), ne) - 1) * (np + 1) + segment_of(pos[j], p[j], mfirst)], p[j],
+                                  mfirst, mlast);
         } else {
             const Axis rows{EE, ne, elo, ehi, bin_inv_width(elo, ehi, ne)};
             const Axis cols{PE, np, plo, phi, bin_inv_width(plo, phi, np)};

@@ -348,6 +348,11 @@ __host__ __device__ __forceinline__ Segment make_segment(const float *P, const f
     return g;
 }
 
+// The segment of x given its number of centres at or below it.  Centres may
+// coincide after rounding, so x at the first centre can count several: up to it
+// the value is the first one.
+__device__ __forceinline__ int segment_of(int pos, float x, float mfirst) { return x > mfirst ? pos : 0; }
+
 // lookup_interp of x given its segment; mfirst, mlast: the outer centres.
 __device__ __forceinline__ float segment_at(const Segment &g, float x, float mfirst, float mlast) {
     const float d = x - g.m0;

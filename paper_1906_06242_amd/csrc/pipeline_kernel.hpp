@@ -228,7 +228,8 @@ __device__ __forceinline__ void jes_lut_n(const QT &Q, const float *E, const flo
     const float mfirst = E[Q.jlc.p], mlast = E[Q.jlc.p + nc - 1];
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        const float *g = E + Q.jseg + 4 * ((min(max(row[n], 1), nr) - 1) * (nc + 1) + pos[n]);
+        const float *g =
+            E + Q.jseg + 4 * ((min(max(row[n], 1), nr) - 1) * (nc + 1) + segment_of(pos[n], pt[n], mfirst));
         out[n] = segment_at(Segment{g[0], g[1], g[2], 0.0f}, pt[n], mfirst, mlast);
     }
 }
