@@ -62,32 +62,36 @@ static bool use_lds_hist(hepk_plan p) {
 }
 
 // Where the kernels' bin guess can be wrong.  The guess for x is
-// floor(g(x)) + 1 with g(x) = (x - lo) * inv_w in float32 (each operation
-// rounded, as on the device), capped at nb; g is monotone in x.  For x in bin
-// i (E[i-1] <= x < E[i]), g(x) lies between A = g(E[i-1]) and B = g(the float
-// below E[i]), so the guess is too high only if B >= i, and then only where
-// f = frac(g) <= B - i, and too low only if A < i - 1, and then only where
-// f >= 1 - (i - 1 - A); the last bin is never too high (the cap).  Returned:
+// floor(c) + 1 with c = g(x) clamped to [-0.5, nb + 0.5] and
+// g(x) = (x - lo) * inv_w in float32 (each operation rounded, as on the
+// device); g is monotone in x.  For x in slot i (E[i-1] <= x < E[i], slot 0
+// below E[0], slot nb + 1 from E[nb] on), g(x) is at least A = g(E[i-1])
+// (i > 0) and at most B = g(the float below E[i]) (i <= nb), so the guess is
+// too high only if B >= i, and then only where f = frac(g) <= B - i, and too
+// low only if A < i - 1, and then only where f >= 1 - (i - 1 - A).  Returned:
 // t with every such f satisfying |f - 0.5| >= t in the kernel's float32
 // (0.5 - f and f - 0.5 round monotonically in f); t > 0.5 flags none of them
-// and t <= 0 all.
-static float guess_bound(const float *e, int nb, float lo, float iw) {
+// and t <= 0 all.  (A clamped guess has f = 0.5 and is right: an error of
+// half a bin or more gives t <= 0.)  nonneg: the values are -inf or not
+// negative, so an axis from 0 has none in the slot below it whose g rounds to
+// -0 and looks like the first bin's.
+static float guess_bound(const float *e, int nb, float lo, float iw, bool nonneg) {
     auto g = [&](float x) {
         const float d = x - lo;
         const float r = d * iw;
         return static_cast<double>(r);
     };
+    if (nb >= (1 << 22)) return -1.0f;  // nb + 0.5 is not a float32
     double dhi = -1.0, dlo = 0.0;
     bool finite = true;
-    for (int i = 1; i <= nb; ++i) {
-        const double a = g(e[i - 1]);
+    for (int i = 0; i <= nb; ++i) {
+        const double a = g(e[i]);  // the bottom of slot i + 1
         finite &= std::isfinite(a);
-        dlo = std::max(dlo, (i - 1) - a);
-        if (i < nb) {
-            const double b = g(std::nextafter(e[i], -INFINITY));
-            finite &= std::isfinite(b);
-            dhi = std::max(dhi, b - i);
-        }
+        dlo = std::max(dlo, i - a);
+        if (i == 0 && nonneg && e[0] <= 0.0f) continue;
+        const double b = g(std::nextafter(e[i], -INFINITY));  // the top of slot i
+        finite &= std::isfinite(b);
+        dhi = std::max(dhi, b - i);
     }
     if (!finite || dhi >= 0.5 || dlo >= 0.5) return -1.0f;
     float t = 1.5f;  // neither side can be wrong
@@ -193,7 +197,9 @@ static void set_qdev(QDev &o, const hepk_query &Q, const float *const edges[3]) 
         o.lo[h] = e[0];
         o.hi[h] = e[nb];
         o.inv_w[h] = (span > 0.0f && std::isfinite(span)) ? static_cast<float>(nb) / span : 0.0f;
-        o.chk[h] = guess_bound(e, nb, o.lo[h], o.inv_w[h]);
+        // (counts, and energies above a jet_pt of 0 or more, are not negative)
+        o.chk[h] = guess_bound(e, nb, o.lo[h], o.inv_w[h], h == 2 || !(Q.jet_pt < 0.0f));
+        o.top[h] = static_cast<float>(nb) + 0.5f;
     }
 }
 

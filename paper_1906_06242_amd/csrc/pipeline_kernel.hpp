@@ -102,11 +102,12 @@ struct QDev {
     int32_t ebase[3];    // first edge of each observable in the plan's edge table
     float lo[3], hi[3];  // first and last edge of each observable
     float inv_w[3];      // nbins / (hi - lo): start value of the bin search
-    // The guess g = (x - lo) * inv_w (float32) can name a wrong bin only
-    // where its fraction f = g - floor(g) has |f - 0.5| >= chk (a bound the
-    // plan derives from the edges, guess_bounds); only such guesses are
-    // checked against the edges.
+    // The guess g = (x - lo) * inv_w (float32), clamped to [-0.5, top], can
+    // name a wrong slot only where its fraction f = g - floor(g) has
+    // |f - 0.5| >= chk (a bound the plan derives from the edges,
+    // guess_bound); only such guesses are checked against the edges.
     float chk[3];
+    float top[3];  // nbins + 0.5
     // Histogram of (scale v, observable h) starts at slot0 + v * per_scale +
     // hoff[h]: in the workgroup's LDS copy (compact over the active queries)
     // and in the dataset's block in HBM (fixed per query slot).
@@ -247,9 +248,9 @@ __device__ __forceinline__ float shifted_pt_bound(float pt, float d, float smin,
 // registers: they are uniform, and without the pin the compiler reloads each
 // field from memory (and waits for it) next to every use.
 struct FillC {
-    int32_t base, per;       // first slot of scale 0, slots per scale (LDS or global layout)
-    int32_t nb[3], eb[3], off[3];
-    float lo[3], hi[3], iw[3], ck[3];
+    int32_t base, per;  // first slot of scale 0, slots per scale (LDS or global layout)
+    int32_t off[3];
+    float lo[3], iw[3], ck[3], top[3];
 };
 
 template <typename X>
@@ -267,56 +268,53 @@ __device__ __forceinline__ FillC fill_consts(const QT &Q) {
     F.per = LDSH ? Q.lper_scale : Q.gper_scale;
 #pragma unroll
     for (int h = 0; h < 3; ++h) {
-        F.nb[h] = Q.nbins[h];
-        F.eb[h] = Q.ebase[h];
         F.off[h] = LDSH ? Q.lhoff[h] : Q.ghoff[h];
         F.lo[h] = Q.lo[h];
-        F.hi[h] = Q.hi[h];
         F.iw[h] = Q.inv_w[h];
         F.ck[h] = Q.chk[h];
+        F.top[h] = Q.top[h];
     }
     asm volatile(""
-                 : "+s"(F.base), "+s"(F.per), "+s"(F.nb[0]), "+s"(F.nb[1]), "+s"(F.nb[2]), "+s"(F.eb[0]),
-                   "+s"(F.eb[1]), "+s"(F.eb[2]), "+s"(F.off[0]), "+s"(F.off[1]), "+s"(F.off[2]), "+s"(F.lo[0]),
-                   "+s"(F.lo[1]), "+s"(F.lo[2]), "+s"(F.hi[0]), "+s"(F.hi[1]), "+s"(F.hi[2]), "+s"(F.iw[0]),
-                   "+s"(F.iw[1]), "+s"(F.iw[2]), "+s"(F.ck[0]), "+s"(F.ck[1]), "+s"(F.ck[2]));
+                 : "+s"(F.base), "+s"(F.per), "+s"(F.off[0]), "+s"(F.off[1]), "+s"(F.off[2]), "+s"(F.lo[0]),
+                   "+s"(F.lo[1]), "+s"(F.lo[2]), "+s"(F.iw[0]), "+s"(F.iw[1]), "+s"(F.iw[2]), "+s"(F.ck[0]),
+                   "+s"(F.ck[1]), "+s"(F.ck[2]), "+s"(F.top[0]), "+s"(F.top[1]), "+s"(F.top[2]));
     return F;
 }
 
 // Slots of N values, x[n] going to observable n % 3 (H_T, lead, nJet): the
-// same slot as hist_slot_lohi.  The guess from the uniform-bin formula is
-// taken as exact unless its fraction is within the plan's bound of 0 or 1
-// (chk), so only lanes with such a guess read edges -- rarely any lane of a
-// wavefront, so the round trip is usually skipped (eight queries, whose edges
-// stay in HBM: 588 -> 544 us per 6.25e6 events against checking every guess).
-// A binary search replaces a guess that was off.  The fills are a third of the
-// multi-scale kernels' instructions, so no operation here is spare: without
-// the range tests that the bound makes redundant, the select chain and the
-// NaN tests 20 scales over 2e7 events took 776 us instead of 885.
-template <int N>
-__device__ __forceinline__ void find_bins(const FillC &F, const float *edges, const float (&x)[N], int (&s)[N]) {
+// same slot as hist_slot_lohi.  The guess from the uniform-bin formula, one bin
+// beyond either end of the axis, is taken as exact unless its fraction is
+// within the plan's bound of 0 or 1 (chk), so only lanes with such a guess
+// read edges -- rarely any lane of a wavefront, so the round trip is usually
+// skipped (eight queries, whose edges stay in HBM: 588 -> 544 us per 6.25e6
+// events against checking every guess).  A value outside the axis is clamped
+// to a fraction of 0.5 and never flagged (clamped to the bins instead, it was
+// whenever the bound flagged anything: 20 scales over 3e6 events with 183 bins
+// up to 300, a tail beyond them, 237 -> 189 us; without a tail 192 -> 184).  A
+// binary search replaces a guess that was off.  The fills are a third of the
+// multi-scale kernels' instructions, so no operation here is spare.
+template <int N, typename QT>
+__device__ __forceinline__ void find_bins(const FillC &F, const QT &Q, const float *edges, const float (&x)[N],
+                                          int (&s)[N]) {
     bool chk = false;  // some value of this lane needs the edges
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-        // branch-free: the guess clamped to the bins, its bin corrected for
-        // values outside the edges (the slot of a NaN x is not used); a clamped
-        // or NaN guess is flagged whenever the bound flags anything
         const int h = n % 3;
         const float g = (x[n] - F.lo[h]) * F.iw[h];
-        const float c = __builtin_amdgcn_fmed3f(g, 0.0f, static_cast<float>(F.nb[h] - 1));
-        s[n] = static_cast<int>(c) + 1 + (x[n] >= F.hi[h] ? 1 : 0) - (x[n] < F.lo[h] ? 1 : 0);
+        const float c = __builtin_amdgcn_fmed3f(g, -0.5f, F.top[h]);
+        s[n] = static_cast<int>(floorf(c)) + 1;
         chk |= !(fabsf(__builtin_amdgcn_fractf(c) - 0.5f) < F.ck[h]);
     }
     if (chk) {
         // every value of the lane by the edges (a right guess is kept)
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            const int h = n % 3;
-            const float *E = edges + F.eb[h];
-            const int k = min(max(s[n], 1), F.nb[h]);
-            const bool in = (x[n] >= F.lo[h]) & (x[n] < F.hi[h]);
-            s[n] = x[n] >= F.hi[h] ? F.nb[h] + 1 : (in ? k : 0);
-            if (in && (x[n] < E[k - 1] || x[n] >= E[k])) s[n] = bin_search(E, F.nb[h], x[n]);
+            const int h = n % 3, nb = Q.nbins[h];
+            const float *E = edges + Q.ebase[h];
+            const int k = min(max(s[n], 1), nb);
+            const bool in = (x[n] >= Q.lo[h]) & (x[n] < Q.hi[h]);
+            s[n] = x[n] >= Q.hi[h] ? nb + 1 : (in ? k : 0);
+            if (in && (x[n] < E[k - 1] || x[n] >= E[k])) s[n] = bin_search(E, nb, x[n]);
         }
     }
 }
@@ -524,12 +522,12 @@ __device__ __forceinline__ bool ht_can_be_nan(float jet_pt) { return jet_pt < -1
 // several scales and LDS histograms every lane adds, zero where it does not
 // fill, at a slot of a scale no later than vlast (the query's last), so no
 // value needs its own branch.
-template <int N, bool MS, bool LDSH, bool W2>
-__device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const FillC &F, const float *edges,
-                                          const float (&xs)[N], const bool (&pass)[N / 3], int v0, double w,
-                                          int vlast) {
+template <int N, bool MS, bool LDSH, bool W2, typename QT>
+__device__ __forceinline__ void fill_bins(const HistSink<LDSH, W2> &sink, const FillC &F, const QT &Q,
+                                          const float *edges, const float (&xs)[N], const bool (&pass)[N / 3], int v0,
+                                          double w, int vlast) {
     int sl[N];
-    find_bins<N>(F, edges, xs, sl);
+    find_bins<N>(F, Q, edges, xs, sl);
     if (MS && LDSH) {
 #pragma unroll
         for (int n = 0; n < N; ++n)
@@ -1362,9 +1360,9 @@ pipeline_kernel(PipeArgs P) {
                     auto fill = [&](const auto &xs, const auto &pass, int v0, double w) __attribute__((always_inline)) {
                         constexpr int N = std::extent<std::remove_reference_t<decltype(xs)>>::value;
                         if (P.edges_in_lds)
-                            fill_bins<N, MS>(sink, F, e_s, xs, pass, v0, w, vlast);
+                            fill_bins<N, MS>(sink, F, Q, e_s, xs, pass, v0, w, vlast);
                         else
-                            fill_bins<N, MS>(sink, F, P.edges, xs, pass, v0, w, vlast);
+                            fill_bins<N, MS>(sink, F, Q, P.edges, xs, pass, v0, w, vlast);
                     };
                     if (ht_can_be_nan(jet_pt)) {
                         // (filled above)
