@@ -1202,8 +1202,10 @@ pipeline_kernel(PipeArgs P) {
                         }
                         nrec += __popcll(b);
                     }
-                    // their candidates, in tile order
-                        int run = 0;
+                    // their candidates, in tile order (the bits below were set
+                    // by other lanes, and the list takes the place of cpre)
+                    wave_sync();
+                    int run = 0;
                     // (the bits of all slots in one read, a 32-bit word per lane)
                     const uint32_t ew = reinterpret_cast<const uint32_t *>(L.em)[lane & 31];
                     const float f = (zsel && !shift) ? smax : 1.0f;
