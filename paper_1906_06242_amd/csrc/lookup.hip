@@ -115,8 +115,7 @@ __global__ __launch_bounds__(LB) void lookup1_kernel(const X *__restrict__ x, in
 // LDS reads bound these kernels before (scale factors of 1.5e7 float16 muons:
 // content 27 -> 21 us, interpolation 37 -> 21 us; floor 13 us for 90 MB).
 // Contents of near-uniform edges keep the uniform-bin guess, which needs no
-// table (80 bins, 1e7 rows: 19 us against 22); edges that no key spreads keep
-// the search.
+// table (80 bins, 1e7 rows: 19 us against 22).
 template <typename X, int MODE, bool VEC>
 __global__ __launch_bounds__(LB) void lookup1_lut_kernel(const X *__restrict__ x, int64_t n,
                                                          const float *__restrict__ E, int nb,
@@ -151,20 +150,14 @@ __global__ __launch_bounds__(LB) void lookup1_lut_kernel(const X *__restrict__ x
     for (int64_t g = static_cast<int64_t>(blockIdx.x) * LB + threadIdx.x; g < ng; g += stride) {
         float v[4], r[4];
         load_quad<X, VEC>(x, g, n, v);
-        if (t.M <= kLutMaxShare) {
-            int pos[4];
-            lut_count_n<4>(t, v, pos);
+        int pos[4];
+        lut_count_n<4>(t, v, pos);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if constexpr (MODE == 0)
-                    r[j] = (v[j] != v[j]) ? __builtin_nanf("") : c_s[pos[j]];
-                else
-                    r[j] = segment_at(g_s[segment_of(pos[j], v[j], mfirst)], v[j], mfirst, mlast);
-            }
-        } else {
-            const Axis a{E, nb, elo, ehi, bin_inv_width(elo, ehi, nb)};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) r[j] = MODE == 0 ? lookup_bin(a, c_s, v[j]) : lookup_interp(a, c_s + 1, v[j]);
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (MODE == 0)
+                r[j] = (v[j] != v[j]) ? __builtin_nanf("") : c_s[pos[j]];
+            else
+                r[j] = segment_at(g_s[segment_of(pos[j], v[j], mfirst)], v[j], mfirst, mlast);
         }
         store_quad<VEC>(out, g, n, r);
     }
@@ -206,51 +199,45 @@ __global__ __launch_bounds__(LB) void jes_delta_kernel(const X *__restrict__ pt,
 // The same with bucket tables for rows and columns and precomputed segments:
 // five LDS reads per element instead of seventeen (7 rows of 24 bins, 5e7
 // float16 jets 171 -> 94 us; floor 58 us for 400 MB).
-constexpr int kMaxSegments = 1024;  // 16 KiB: still eight workgroups per CU
+// (16 KiB of segments and the 2.5 KB of the other tables: eight workgroups in
+// the 160 KiB of a CU.)
+constexpr int kMaxSegments = 1024;
 
 template <typename X, bool VEC>
 __global__ __launch_bounds__(LB) void jes_lut_kernel(const X *__restrict__ pt, const X *__restrict__ eta, int64_t n,
                                                      const float *__restrict__ EE, int ne,
                                                      const float *__restrict__ PE, int np,
                                                      const float *__restrict__ D, float *__restrict__ out) {
-    extern __shared__ Segment seg_s[];  // ne rows of np + 1
+    extern __shared__ Segment seg_s[];  // make_lut's scratch, then ne rows of np + 1
     __shared__ float r_s[kLutMaxPoints + 2], p_s[kLutMaxPoints + 2];
     __shared__ uint8_t rl_s[kLutKeys], pl_s[kLutKeys];
-    __shared__ LutScratch w_s;
     stage(r_s, EE, ne + 1);
     for (int i = threadIdx.x; i < np; i += LB) p_s[i] = bin_centre(PE[i], PE[i + 1]);
     __syncthreads();
+    LutScratch &w_s = *reinterpret_cast<LutScratch *>(seg_s);
+    const PointLut tr = make_lut(r_s, ne + 1, rl_s, w_s);
+    const PointLut tp = make_lut(p_s, np, pl_s, w_s);
     for (int i = threadIdx.x; i < ne * (np + 1); i += LB) {
         const int row = i / (np + 1);
         seg_s[i] = make_segment(p_s, D + static_cast<int64_t>(row) * np, np, i - row * (np + 1));
     }
-    const PointLut tr = make_lut(r_s, ne + 1, rl_s, w_s);
-    const PointLut tp = make_lut(p_s, np, pl_s, w_s);
-    const bool lut = tr.M <= kLutMaxShare && tp.M <= kLutMaxShare;
+    __syncthreads();
     const float mfirst = p_s[0], mlast = p_s[np - 1];
-    const float elo = as_const(EE)[0], ehi = as_const(EE)[ne];
-    const float plo = as_const(PE)[0], phi = as_const(PE)[np];
     const int64_t ng = (n + 3) >> 2;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * LB;
     for (int64_t g = static_cast<int64_t>(blockIdx.x) * LB + threadIdx.x; g < ng; g += stride) {
         float p[4], h[4], r[4];
         load_quad<X, VEC>(pt, g, n, p);
         load_quad<X, VEC>(eta, g, n, h);
-        if (lut) {
-            int row[4], pos[4];
+        int row[4], pos[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) h[j] = (h[j] != h[j]) ? -INFINITY : fabsf(h[j]);  // NaN: the first row
-            lut_count_n<4>(tr, h, row);
-            lut_count_n<4>(tp, p, pos);
+        for (int j = 0; j < 4; ++j) h[j] = (h[j] != h[j]) ? -INFINITY : fabsf(h[j]);  // NaN: the first row
+        lut_count_n<4>(tr, h, row);
+        lut_count_n<4>(tp, p, pos);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                r[j] = segment_at(seg_s[(min(max(row[j], 1), ne) - 1) * (np + 1) + segment_of(pos[j], p[j], mfirst)], p[j],
-                                  mfirst, mlast);
-        } else {
-            const Axis rows{EE, ne, elo, ehi, bin_inv_width(elo, ehi, ne)};
-            const Axis cols{PE, np, plo, phi, bin_inv_width(plo, phi, np)};
-            lookup2_n<4>(rows, cols, D, p, h, r);
-        }
+        for (int j = 0; j < 4; ++j)
+            r[j] = segment_at(seg_s[(min(max(row[j], 1), ne) - 1) * (np + 1) + segment_of(pos[j], p[j], mfirst)], p[j],
+                              mfirst, mlast);
         store_quad<VEC>(out, g, n, r);
     }
 }
@@ -305,7 +292,7 @@ static int launch_jes(const void *pt, const void *eta, int64_t n, const float *E
     const int64_t segs = static_cast<int64_t>(ne) * (np + 1);
     if (ne < kLutMaxPoints && np <= kLutMaxPoints && segs <= kMaxSegments && n >= kLutMinRows) {
         const int lg = lookup_grid(n, kLutWgPerCu);
-        const size_t sb = static_cast<size_t>(segs) * sizeof(Segment);
+        const size_t sb = std::max(static_cast<size_t>(segs) * sizeof(Segment), sizeof(LutScratch));
         if (vec) jes_lut_kernel<X, true><<<lg, LB, sb, s>>>(p, h, n, EE, ne, PE, np, D, out);
         else jes_lut_kernel<X, false><<<lg, LB, sb, s>>>(p, h, n, EE, ne, PE, np, D, out);
     } else if (lds && vec) jes_delta_kernel<X, true, true><<<grid, LB, lb, s>>>(p, h, n, EE, ne, PE, np, D, out);

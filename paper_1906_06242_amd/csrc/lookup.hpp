@@ -232,14 +232,15 @@ __device__ __forceinline__ void lookup2_n(const Axis &rows, const Axis &cols, co
 // Number of points P[0..np) (ascending) at or below x, by a bucket table: a
 // monotone key puts every float into one of kLutKeys buckets, L[k] is the number
 // of points with a smaller key -- all of them at or below any x of bucket k --
-// and at most M points share a bucket, so M compares finish the count.  The key
+// and at most M points share a bucket, so M compares finish the count -- or,
+// where no key spreads the points, a binary search among the bucket's.  The key
 // is either linear between the first and last point or the float's own bits
 // (even steps of its logarithm), whichever spreads the points better; both are
 // monotone as computed (each operation rounds monotonically), which is all
 // the count needs.
 constexpr int kLutKeys = 256;
 constexpr int kLutMaxPoints = 255;  // counts are bytes
-constexpr int kLutMaxShare = 4;     // more compares than this: the binary search is as good
+constexpr int kLutMaxShare = 4;     // more compares than this: the binary search
 
 struct PointLut {
     const float *P;    // np points, then a NaN (never at or below x)
@@ -272,7 +273,7 @@ struct LutScratch {
 };
 
 // Builds the table (the whole workgroup; P[0..np) filled and synchronised,
-// P[np] writable, 1 <= np <= kLutMaxPoints).  M above kLutMaxShare: not suited.
+// P[np] writable, 1 <= np <= kLutMaxPoints).
 __device__ __forceinline__ PointLut make_lut(float *P, int np, uint8_t *L, LutScratch &w) {
     PointLut t;
     t.P = P;
@@ -316,17 +317,32 @@ __device__ __forceinline__ PointLut make_lut(float *P, int np, uint8_t *L, LutSc
     return t;
 }
 
-// pos[n] = number of points at or below x[n] (NaN: any number up to np).
-template <int N>
+// pos[n] = number of points at or below x[n] (NaN: any number up to np).  The
+// binary search may look past the bucket (later points are above x) and past
+// the points (the NaN there is not at or below anything).  5e7 rows in a table
+// with 30 points in one bucket: contents 78 us, interpolation 81, 2-D shift 121
+// (the search over all edges in LDS 80, 116 and 168).  FEW: M is at most
+// kLutMaxShare (the tables of a plan).
+template <int N, bool FEW = false>
 __device__ __forceinline__ void lut_count_n(const PointLut &t, const float (&x)[N], int (&pos)[N]) {
 #pragma unroll
     for (int n = 0; n < N; ++n) pos[n] = t.L[min(max(t.key(x[n]), 0), kLutKeys - 1)];
-    for (int m = 0; m < t.M; ++m) {
+    if (FEW || t.M <= kLutMaxShare) {
+        for (int m = 0; m < t.M; ++m) {
+            float e[N];
+#pragma unroll
+            for (int n = 0; n < N; ++n) e[n] = t.P[pos[n]];
+#pragma unroll
+            for (int n = 0; n < N; ++n) pos[n] += e[n] <= x[n] ? 1 : 0;
+        }
+        return;
+    }
+    for (int step = 1 << (31 - __builtin_clz(t.M)); step > 0; step >>= 1) {
         float e[N];
 #pragma unroll
-        for (int n = 0; n < N; ++n) e[n] = t.P[pos[n]];
+        for (int n = 0; n < N; ++n) e[n] = t.P[min(pos[n] + step - 1, t.np)];
 #pragma unroll
-        for (int n = 0; n < N; ++n) pos[n] += e[n] <= x[n] ? 1 : 0;
+        for (int n = 0; n < N; ++n) pos[n] += e[n] <= x[n] ? step : 0;
     }
 }
 

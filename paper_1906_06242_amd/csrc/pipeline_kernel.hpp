@@ -223,8 +223,8 @@ __device__ __forceinline__ void jes_lut_n(const QT &Q, const float *E, const flo
     int row[N], pos[N];
 #pragma unroll
     for (int n = 0; n < N; ++n) ae[n] = (eta[n] != eta[n]) ? -INFINITY : fabsf(eta[n]);  // NaN: the first row
-    lut_count_n<N>(lut_at(Q.jlr, E), ae, row);
-    lut_count_n<N>(lut_at(Q.jlc, E), pt, pos);
+    lut_count_n<N, true>(lut_at(Q.jlr, E), ae, row);
+    lut_count_n<N, true>(lut_at(Q.jlc, E), pt, pos);
     const int nr = Q.jr_nb, nc = Q.jc_nb;
     const float mfirst = E[Q.jlc.p], mlast = E[Q.jlc.p + nc - 1];
 #pragma unroll
