@@ -449,7 +449,7 @@ struct Caps {
     static constexpr int EK = EXT ? 2 * EVPL : 1;    // electron slots per lane
     static constexpr int JC = 64 * JK, MC = 64 * MK, EC = 64 * EK;
     // Dense candidates per pass over the tile's events (a tile with more takes
-    // its events in several passes).  The base selection lists 86 of a
+    // its events in several passes, each as many as fit).  The base selection lists 86 of a
     // 64-event tile on average (99%: 123), the extended one 47 (83).
     // (The extended schema at two events per lane runs one workgroup per CU
     // whatever its list: it takes what 60 histograms leave of the LDS.)
@@ -987,9 +987,9 @@ pipeline_kernel(PipeArgs P) {
             (void)jbt;
             (void)lpt;
             // Per query, the events [wlo, whi) of the tile: all of them, unless
-            // they list more candidates than the dense list holds; then half as
-            // many, and the others in further passes.
-            int wlo = 0, whi = TW;
+            // they list more candidates than the dense list holds; then as many
+            // as fit, and the others in further passes.
+            int wlo = 0;
             for (int q = 0; q < P.n_q;) {
                 // (values derived from the lane index and from the events'
                 // ranges are recomputed per query rather than held across the
@@ -1120,7 +1120,7 @@ pipeline_kernel(PipeArgs P) {
                     const uint32_t cw0 = L.cpre[jb[r]], cw1 = L.cpre[je[r]];
                     const int nc = static_cast<int>((cw1 & 0xffffu) - (cw0 & 0xffffu));
                     elig[r] = (lane + 64 * r < ne) & (nmu[r] >= min_mu) & (je[r] - jb[r] >= min_jet) &
-                              (lane + 64 * r >= wlo) & (lane + 64 * r < whi);
+                              (lane + 64 * r >= wlo);
                     if (!DBG)
                         elig[r] = elig[r] & (nc >= min_jet) &
                                   (!EXT | (static_cast<int>((cw1 >> 16) - (cw0 >> 16)) >= min_b));
@@ -1143,7 +1143,7 @@ pipeline_kernel(PipeArgs P) {
                     start[r] = total + incl - cnt[r];
                     total += __builtin_amdgcn_readlane(incl, 63);
                     some |= elig[r];
-                    if (DBG && lane + 64 * r < min(ne, whi) && lane + 64 * r >= wlo) {
+                    if (DBG && lane + 64 * r < ne && lane + 64 * r >= wlo) {
                         // the muon count and weight of every event; the rest
                         // only of events that are not walked (the walk writes
                         // the other fields of walked events' records)
@@ -1161,7 +1161,30 @@ pipeline_kernel(PipeArgs P) {
                             }
                         }
                     }
-                    // their jets' bits
+                }
+                int whi = TW;
+                if (total > CAP) {
+                    // the events up to the first that does not fit (every event
+                    // has at most CAP jets, so the first one always fits)
+                    int fit_total = total;
+                    some = false;
+#pragma unroll
+                    for (int r = EVPL - 1; r >= 0; --r) {
+                        const bool fit = start[r] + cnt[r] <= CAP;
+                        const int nf = __popcll(__ballot(fit));
+                        if (nf < 64) {
+                            whi = 64 * r + nf;
+                            fit_total = __builtin_amdgcn_readlane(start[r], nf);
+                        }
+                        elig[r] = elig[r] & fit;
+                        cnt[r] = fit ? cnt[r] : 0;
+                        some |= elig[r];
+                    }
+                    total = fit_total;
+                }
+                // their jets' bits
+#pragma unroll
+                for (int r = 0; r < EVPL; ++r)
                     if (cnt[r] > 0) {
                         const int ja = jb[r], jz = je[r] - 1;
                         const int wa = ja >> 6, wz = jz >> 6;
@@ -1172,14 +1195,6 @@ pipeline_kernel(PipeArgs P) {
                             or_u64(&L.em[wz], hi);
                         }
                     }
-                }
-                if (total > CAP) {
-                    // (every event has at most CAP jets, so a pass over one
-                    // event always fits)
-                    whi = wlo + (min(whi, ne) - wlo + 1) / 2;
-                    wave_sync();
-                    continue;
-                }
                 const bool any_ev = __ballot(some) != 0;
                 const bool last_pass = whi >= ne;
                 // With one scale and jet_pt >= 0 (zsel) the cone test decides
@@ -1509,7 +1524,6 @@ pipeline_kernel(PipeArgs P) {
                 } else {
                     wlo = whi;
                 }
-                whi = TW;
                 wave_sync();
             }
         };
