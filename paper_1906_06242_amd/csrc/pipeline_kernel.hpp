@@ -350,10 +350,11 @@ __device__ __forceinline__ float lane_f(float x, int l) {
 }
 
 // One event by the whole wavefront, columns read straight from HBM (events
-// beyond the on-chip capacity): a lane per object, 64 at a time, the selected
-// ones then taken in order for the sums and products.  Everything but the
-// lanes' own objects is uniform.  LK: lookup event weights and, with jes_mode
-// 1, shifted jet energies.
+// beyond the on-chip capacity): a lane per object, 64 at a time, for the cuts,
+// the cone test and the lookups; then a lane per jet-energy scale takes the
+// jets that are left one by one, in order, so that all scales share one
+// reading of the columns.  LK: lookup event weights and, with jes_mode 1,
+// shifted jet energies.
 template <typename T, bool EXT, bool LDSH, bool DBG, bool LK>
 __device__ __forceinline__ void event_direct(const PipeArgs &P, const DsDev &D, int64_t e, int lane,
                                              const float *edges, const HistSink<LDSH, LK> &sink) {
@@ -398,37 +399,53 @@ __device__ __forceinline__ void event_direct(const PipeArgs &P, const DsDev &D, 
         if (LK && Q.pu_nb > 0 && D.npu) wq = wq * lookup_bin(ax.pu, edges + Q.pu_c, as_const(D.npu)[e]);
         if (use_sf) wq = wq * prod;
         const bool shift = LK && Q.jes_mode == 1;
-        for (int v = 0; v < Q.n_scale; ++v) {
-            const float s = as_const(P.scales)[Q.scale0 + v];
+        const int V = Q.n_scale;
+        for (int v0 = 0; v0 < V; v0 += 64) {
+            const int v = v0 + lane;
+            const float s = P.scales[Q.scale0 + min(v, V - 1)];
             int nj = 0, nb = 0;
             float ht = 0.0f, lead = -INFINITY;
             for (int64_t j = 0; j < nj_all; j += 64) {
                 const int64_t i = j + lane;
-                float x = 0.0f, eta = 0.0f;
-                bool sel = false;
+                float pt = 0.0f, eta = 0.0f, phi = 0.0f, d = 0.0f;
+                bool keep = false, tag = false;
                 if (i < nj_all) {
-                    const float pt = ldf(jpt, i);
+                    pt = ldf(jpt, i);
                     eta = ldf(jeta, i);
-                    x = shift ? pt * (1.0f + s * jes_shift(ax, edges, Q.jd, pt, eta)) : pt * s;
-                    sel = x > Q.jet_pt && fabsf(eta) < Q.jet_abseta;
+                    phi = ldf(jphi, i);
+                    keep = (pt >= Q.ptmin) & (fabsf(eta) < Q.jet_abseta);
+                    if (has_bt) tag = ldf(jbt, i) > Q.btag;
                 }
-                const float phi = sel ? ldf(jphi, i) : 0.0f;
-                if (__ballot(sel) == 0) continue;
-                for (int64_t m = 0; m < nm_all; ++m)
-                    if (mu_sel(m)) sel = sel && !(delta_r2(eta, phi, ldf(meta, m), ldf(mphi, m)) <= Q.thr2);
-                for (int64_t m = 0; m < nl_all; ++m)
-                    if (el_sel(m)) sel = sel && !(delta_r2(eta, phi, ldf(eeta, m), ldf(ephi, m)) <= Q.thr2);
-                if (has_bt) nb += __popcll(__ballot(sel && ldf(jbt, sel ? i : 0) > Q.btag));
-                uint64_t b = __ballot(sel);
-                nj += __popcll(b);
-                for (; b; b &= b - 1) {
-                    const float xl = lane_f(x, __builtin_ctzll(b));
-                    ht = ht + xl;
-                    lead = fmaxf(lead, xl);
+                if (__ballot(keep) == 0) continue;
+                // (leptons 64 at a time too, the selected ones broadcast)
+                auto cone = [&](int64_t n, const T *le, const T *lp, auto &&sel) {
+                    for (int64_t m = 0; m < n; m += 64) {
+                        const bool in = m + lane < n;
+                        const float ve = in ? ldf(le, m + lane) : 0.0f, vp = in ? ldf(lp, m + lane) : 0.0f;
+                        for (uint64_t b = __ballot(in && sel(m + lane)); b; b &= b - 1) {
+                            const int l = __builtin_ctzll(b);
+                            keep = keep & !(delta_r2(eta, phi, lane_f(ve, l), lane_f(vp, l)) <= Q.thr2);
+                        }
+                    }
+                };
+                cone(nm_all, meta, mphi, mu_sel);
+                if (EXT) cone(nl_all, eeta, ephi, el_sel);
+                if (shift && keep) d = jes_shift(ax, edges, Q.jd, pt, eta);
+                const uint64_t tags = __ballot(keep && tag);
+                for (uint64_t b = __ballot(keep); b; b &= b - 1) {
+                    const int l = __builtin_ctzll(b);
+                    const float p = lane_f(pt, l);
+                    const float x = shift ? p * (1.0f + s * lane_f(d, l)) : p * s;
+                    const bool sel = x > Q.jet_pt;
+                    const float hs = ht + x;
+                    ht = sel ? hs : ht;
+                    lead = sel ? fmaxf(lead, x) : lead;
+                    nj += sel ? 1 : 0;
+                    nb += sel ? static_cast<int>((tags >> l) & 1u) : 0;
                 }
             }
             const bool pass = nmu >= Q.min_mu && nj >= Q.min_jet && (!has_bt || nb >= Q.min_b);
-            if (lane == 0) {
+            if (v < V) {
                 if (DBG)
                     *rec_at(P, Q.scale0 + v, D.ev0 + e) =
                         hepk_event_record{nmu, nj, nb, pass ? 3 : 2, ht, lead, wq, 0};
@@ -1532,9 +1549,9 @@ pipeline_kernel(PipeArgs P) {
         // register capacity runs as consecutive sub-tiles: from its first
         // event not yet run, the event count is halved until the objects fit
         // (a few scalar loads), that sub-tile runs like a tile, and the rest
-        // of the tile follows.  Only a single event beyond the capacity (and a
-        // tile with an event of more jets than the dense list holds) goes
-        // event by event, straight from HBM.
+        // of the tile follows.  Only a single event beyond the capacity, or
+        // with more candidates than the dense list holds, goes straight from
+        // HBM.
         int r = wave;  // this wavefront's tile (relative to c_t0)
         int eo = 0;    // events of tile r already run
         TileBounds nb{};
@@ -1557,34 +1574,56 @@ pipeline_kernel(PipeArgs P) {
                 n = (n + 1) >> 1;
                 B = tile_bounds<EXT>(D, has_el, e, n);
             }
-            // the position after this (sub-)tile; nb holds the bounds of
-            // tile r + WAVES whenever it starts a tile
-            int r2 = r, eo2 = eo + n;
-            if (eo2 >= tn) {
-                r2 = r + WAVES;
-                eo2 = 0;
-            }
-            // an event with more jets than the dense list holds, or objects
-            // beyond the registers: event by event, straight from HBM (the
-            // tile's loads are issued all the same -- of no object when it is
-            // oversized -- so that one path defines R)
+            // (the loads are issued also of a single event beyond the
+            // registers -- of no object -- so that one path defines R)
             const bool over = oversize(B);
             if (over) B.nj = B.nm = B.nl = 0;
             Raw R;
             issue(e, n, B, R);
             settle(R);
+            // of the events with more jets than the dense list holds, the first
+            // that lists too many for some query ends the sub-tile or, as its
+            // first event, goes alone
             bool direct = over;
 #pragma unroll
-            for (int i = 0; i < EVPL; ++i)
-                direct |= (lane + 64 * i < n) & (R.j1[i] - R.j0[i] > static_cast<uint32_t>(CAP));
-            if (__ballot(direct)) {
+            for (int i = 0; i < EVPL; ++i) {
+                uint64_t lb = __ballot((lane + 64 * i < n) & (R.j1[i] - R.j0[i] > static_cast<uint32_t>(CAP)));
+                for (; lb != 0 && !over; lb &= lb - 1) {
+                    const int l = __builtin_ctzll(lb);
+                    const int ja = static_cast<int>(__builtin_amdgcn_readlane(R.j0[i], l) - static_cast<uint32_t>(B.J0));
+                    const int jz = static_cast<int>(__builtin_amdgcn_readlane(R.j1[i], l) - static_cast<uint32_t>(B.J0));
+                    bool beyond = false;
+                    for (int q = 0; q < P.n_q; ++q) {
+                        const auto &Q = as_const(P.qs)[q];
+                        int nc = 0;
+#pragma unroll
+                        for (int k = 0; k < JK; ++k) {
+                            const int j = lane + 64 * k;
+                            nc += __popcll(__ballot((j >= ja) & (j < jz) & (fabsf(raw_f<T>(R.jeta[k])) < Q.jet_abseta) &
+                                                    (raw_f<T>(R.jpt[k]) >= Q.ptmin)));
+                        }
+                        beyond |= (nc > CAP) & (Q.active != 0);
+                    }
+                    if (beyond) {
+                        direct = 64 * i + l == 0;
+                        n = direct ? 1 : 64 * i + l;
+                        break;
+                    }
+                }
+            }
+            if (direct) {
                 const DsDev Dc = D;
-                for (int i = 0; i < n; ++i) event_direct<T, EXT, LDSH, DBG, LK>(P, Dc, e + i, lane, edges, sink);
+                event_direct<T, EXT, LDSH, DBG, LK>(P, Dc, e, lane, edges, sink);
             } else {
                 work(e, n, B, R);
             }
-            r = r2;
-            eo = eo2;
+            // the next (sub-)tile; nb holds the bounds of tile r + WAVES
+            // whenever it starts a tile
+            eo += n;
+            if (eo >= tn) {
+                r += WAVES;
+                eo = 0;
+            }
         }
         // merge the LDS histograms into the dataset's block in HBM (the next
         // chunk, if any, is another dataset)
