@@ -54,11 +54,57 @@ static size_t hist_lds_bytes(hepk_plan p) {
     return static_cast<size_t>(p->lds_slots) * ((p->lk ? 2 : 1) * sizeof(double) + sizeof(uint32_t));
 }
 
+// LDS bytes of a workgroup's candidate lists, cap candidates each.
+static size_t list_lds_bytes(hepk_plan p, int cap) {
+    const bool h = p->dtype == HEPK_F16;
+    const bool two = p->tune.ev_per_thread == 2;
+    auto of = [&](auto lk) {
+        constexpr bool LK = decltype(lk)::value;
+        if (two)  // (float32 in LDS whatever the content)
+            return p->ext ? list_bytes<float, 2, true, LK>(cap) : list_bytes<float, 2, false, LK>(cap);
+        if (!p->ext) return list_bytes<float, 1, false, LK>(cap);
+        return h ? list_bytes<_Float16, 1, true, LK>(cap) : list_bytes<float, 1, true, LK>(cap);
+    };
+    return static_cast<size_t>(p->tune.block / 64) * (p->lk ? of(std::true_type{}) : of(std::false_type{}));
+}
+
+static int list_min(hepk_plan p) {
+    if (p->tune.ev_per_thread == 2) return p->ext ? Caps<2, true>::CAP_MIN : Caps<2, false>::CAP_MIN;
+    return p->ext ? Caps<1, true>::CAP_MIN : Caps<1, false>::CAP_MIN;
+}
+
+// Dynamic LDS of a workgroup before its candidate lists (16-byte aligned).
+static size_t dyn_lds_bytes(hepk_plan p, bool ldsh) {
+    return ((ldsh ? hist_lds_bytes(p) : 0) + table_lds_bytes(p) + 15) & ~size_t(15);
+}
+
+// LDS of a workgroup whose lists hold cap candidates.
+static size_t wg_lds_bytes(hepk_plan p, bool ldsh, int cap) {
+    return (ldsh ? p->lds_static_lds : p->lds_static_glob) + dyn_lds_bytes(p, ldsh) + list_lds_bytes(p, cap);
+}
+
 // LDS histograms when asked for, within their budget, and when the kernel's
-// own LDS, the histograms and the tables fit in one workgroup's LDS.
+// own LDS, the histograms, the tables and the smallest lists fit in one
+// workgroup's LDS.
 static bool use_lds_hist(hepk_plan p) {
     return p->tune.hist_mode == 0 && hist_lds_bytes(p) <= static_cast<size_t>(kMaxLdsHistBytes) &&
-           p->lds_static_lds + hist_lds_bytes(p) + table_lds_bytes(p) <= p->lds_max;
+           wg_lds_bytes(p, true, list_min(p)) <= p->lds_max;
+}
+
+// Candidates a list holds: as many as leave the CU the workgroups it runs with
+// the smallest lists (the LDS is allocated in steps of kLdsStep), at most all
+// jets of a tile.  The list decides what dense events and loose cuts cost: a
+// tile whose candidates do not fit repeats the selection in further passes
+// (3e6 events without cuts, 285 candidates a tile: base 105 us with lists of
+// 192, extended 200 with 128).
+constexpr size_t kLdsStep = 1280;
+static int list_fit(hepk_plan p, bool ldsh) {
+    int cap = list_min(p);
+    const size_t least = (wg_lds_bytes(p, ldsh, cap) + kLdsStep - 1) / kLdsStep * kLdsStep;
+    const size_t n = std::max<size_t>(1, std::min<size_t>(p->lds_cu / least, ldsh ? p->regs_lds : p->regs_glob));
+    const size_t most = std::min(p->lds_max, p->lds_cu / n / kLdsStep * kLdsStep);
+    while (cap + 64 <= p->list_most && wg_lds_bytes(p, ldsh, cap + 64) <= most) cap += 64;
+    return cap;
 }
 
 // Where the kernels' bin guess can be wrong.  The guess for x is
@@ -359,10 +405,15 @@ Launch make_launch(hepk_plan p, int32_t c0, int32_t c1, double *sumw, uint64_t *
     const int64_t n_tiles = p->tile_pre[c1] - p->tile_pre[c0];
     L.grid = static_cast<int>(
         std::max<int64_t>(1, std::min<int64_t>(p->grid, ceil_div(n_tiles, std::min(p->tune.block / 64, 8)))));
-    L.lds = (ldsh ? hist_lds_bytes(p) : 0) + table_lds_bytes(p);
+    const int cap = list_fit(p, ldsh);
+    const size_t lists = list_lds_bytes(p, cap);
+    L.lds = dyn_lds_bytes(p, ldsh) + lists;
     L.lds_static = ldsh ? p->lds_static_lds : p->lds_static_glob;
     L.lds_max = p->lds_max;
     L.a = p->args;
+    L.a.list_at = static_cast<int32_t>(dyn_lds_bytes(p, ldsh));
+    L.a.list_bytes = static_cast<int32_t>(lists / (p->tune.block / 64));
+    L.a.list_cap = cap;
     L.a.chunk_begin = c0;
     L.a.chunk_end = c1;
     L.a.ds_slots = ldsh ? p->lds_slots : 0;
@@ -579,12 +630,13 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
         p->fn_lds_dbg = pick_dbg(dtype, ext, t.block, t.ev_per_thread, true);
         p->fn_glob_dbg = pick_dbg(dtype, ext, t.block, t.ev_per_thread, false);
         hipFuncAttributes fa{}, fg{}, fad{}, fgd{};
-        int mx = 0;
+        int mx = 0, mcu = 0;
         if (hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(p->fn_lds)) != hipSuccess ||
             hipFuncGetAttributes(&fg, reinterpret_cast<const void *>(p->fn_glob)) != hipSuccess ||
             hipFuncGetAttributes(&fad, reinterpret_cast<const void *>(p->fn_lds_dbg)) != hipSuccess ||
             hipFuncGetAttributes(&fgd, reinterpret_cast<const void *>(p->fn_glob_dbg)) != hipSuccess ||
-            hipDeviceGetAttribute(&mx, hipDeviceAttributeMaxSharedMemoryPerBlock, p->device) != hipSuccess) {
+            hipDeviceGetAttribute(&mx, hipDeviceAttributeMaxSharedMemoryPerBlock, p->device) != hipSuccess ||
+            hipDeviceGetAttribute(&mcu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, p->device) != hipSuccess) {
             set_error("hepk_plan_create: kernel or device attribute query failed");
             return plan_fail(p, HEPK_EHIP);
         }
@@ -593,15 +645,17 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
         // the record kernels take the same launch only with the same LDS
         p->dbg_ok = fad.sharedSizeBytes == fa.sharedSizeBytes && fgd.sharedSizeBytes == fg.sharedSizeBytes;
         p->lds_max = static_cast<size_t>(mx);
+        p->lds_cu = static_cast<size_t>(std::max(mx, mcu));
+        const size_t least_lists = list_lds_bytes(p, list_min(p));
         // the tables go to LDS only if they fit beside the kernel's own LDS
         p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(p->lk ? kMaxLdsLookupBytes : kMaxLdsEdgeBytes);
         p->scales_lds = static_cast<size_t>(p->n_scales) * sizeof(float) <= static_cast<size_t>(kMaxLdsScaleBytes);
-        if (p->lds_static_glob + table_lds_bytes(p) > p->lds_max) p->edges_lds = p->scales_lds = false;
+        if (p->lds_static_glob + least_lists + dyn_lds_bytes(p, false) > p->lds_max) p->edges_lds = p->scales_lds = false;
         // (large lookup tables leave LDS to the histograms when both do not fit)
         if (p->edges_lds && static_cast<size_t>(p->n_edges) * sizeof(float) > static_cast<size_t>(kMaxLdsEdgeBytes) &&
             t.hist_mode == 0 && !use_lds_hist(p))
             p->edges_lds = false;
-        if (p->lds_static_glob + table_lds_bytes(p) > p->lds_max) {
+        if (p->lds_static_glob + least_lists + dyn_lds_bytes(p, false) > p->lds_max) {
             set_error("hepk_plan_create: kernel needs %zu bytes of LDS, device has %zu", p->lds_static_glob,
                       p->lds_max);
             return plan_fail(p, HEPK_EUNSUPPORTED);
@@ -610,17 +664,25 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
         t.block = t.block == 1024 ? 512 : 256;
         p->tune = t;
     }
-    const size_t lds_hist = use_lds_hist(p) ? hist_lds_bytes(p) : 0;
-    const size_t lds_bytes = lds_hist + table_lds_bytes(p);
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(use_lds_hist(p) ? p->fn_lds : p->fn_glob), t.block,
-            lds_bytes) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    // six wavefronts per SIMD at most (only 256-thread workgroups of the base
-    // kernel reach a seventh): 5e6 events 138 us with seven, 117 with six
-    per_cu = std::max(1, std::min(per_cu, 24 / (t.block / 64)));
+    // Workgroups per CU: what the registers allow -- six wavefronts per SIMD
+    // at most (only 256-thread workgroups of the base kernel reach a seventh:
+    // 5e6 events 138 us with seven, 117 with six) -- and the LDS with the
+    // smallest lists; longer lists must not cost a workgroup.
+    auto per_cu_at = [&](bool ldsh, size_t lds) {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &n, reinterpret_cast<const void *>(ldsh ? p->fn_lds : p->fn_glob), t.block, lds) != hipSuccess)
+            n = 1;
+        return std::max(1, std::min(n, 24 / (t.block / 64)));
+    };
+    p->regs_lds = per_cu_at(true, 0);
+    p->regs_glob = per_cu_at(false, 0);
+    const bool ldsh = use_lds_hist(p);
+    const size_t dyn = dyn_lds_bytes(p, ldsh);
+    const int per_cu = per_cu_at(ldsh, dyn + list_lds_bytes(p, list_min(p)));
+    p->list_most = 64 * (6 * t.ev_per_thread + 1);
+    for (int cap = list_fit(p, ldsh); cap > list_min(p) && per_cu_at(ldsh, dyn + list_lds_bytes(p, cap)) < per_cu;)
+        p->list_most = cap -= 64;
     int64_t grid = t.grid > 0 ? t.grid : static_cast<int64_t>(per_cu) * device_cus();
 
     // Work: one chunk per dataset (its tiles), with the tiles of the datasets

@@ -145,6 +145,9 @@ struct PipeArgs {
     int32_t chunk_begin, chunk_end;  // chunks [chunk_begin, chunk_end) of `chunks`
     int32_t n_q, ds_slots, n_edges, edges_in_lds;  // ds_slots: LDS histogram slots
     int32_t n_scales, scales_in_lds;               // the scale table, copied to LDS when small
+    // the candidate lists in dynamic LDS: byte offset of the first wavefront's,
+    // bytes of each, candidates each holds (list_fit)
+    int32_t list_at, list_bytes, list_cap;
     double *sumw;
     uint64_t *counts;
     double *sumw2;  // LK kernels: sums of squared weights (NULL: not kept)
@@ -465,17 +468,48 @@ struct Caps {
     static constexpr int MK = 2 * EVPL;              // muon slots per lane
     static constexpr int EK = EXT ? 2 * EVPL : 1;    // electron slots per lane
     static constexpr int JC = 64 * JK, MC = 64 * MK, EC = 64 * EK;
-    // Dense candidates per pass over the tile's events (a tile with more takes
-    // its events in several passes, each as many as fit).  The base selection lists 86 of a
-    // 64-event tile on average (99%: 123), the extended one 47 (83).
-    // (The extended schema at two events per lane runs one workgroup per CU
-    // whatever its list: it takes what 60 histograms leave of the LDS.)
-    static constexpr int CAP = EXT ? (EVPL == 1 ? 128 : 576) : 192 * EVPL;
-    static constexpr int SW = CAP / 64;  // 64-candidate words
+    // The least the dense list of candidates holds (a tile with more takes
+    // its events in several passes, each as many as fit); a launch takes as
+    // much as the LDS leaves at its occupancy, up to all JC jets (list_fit).
+    // The base selection lists 86 candidates of a 64-event tile on average
+    // (99%: 123), the extended one 47 (83), a selection without cuts all 320.
+    // (The extended schema at two events per lane runs one 512-thread workgroup
+    // per CU whatever its list.)
+    static constexpr int CAP_MIN = EXT ? (EVPL == 1 ? 128 : 576) : (EVPL == 1 ? 192 : 256);
 };
 
 template <bool P>
 using cpre_t = std::conditional_t<P, uint32_t, uint16_t>;
+
+// eta and phi in LDS: the content's own type in the extended schema at one
+// event per lane (LDS is what limits its wavefronts), else float32 (float16
+// copies would take registers beside the values of the cuts).
+template <typename T, int EVPL, bool EXT>
+using lds_t = std::conditional_t<EXT && EVPL == 1, T, float>;
+
+// A dense candidate: pt until the cone test, then NaN for a removed one (with
+// one scale and jet_pt >= 0: pt * s, +0 for a removed one), eta, phi, and with
+// lookups the energy shift.  The b-tags are bytes of their own behind the list.
+template <typename TL, bool LK>
+struct Cand {
+    float pt;
+    TL eta, phi;
+};
+template <typename TL>
+struct Cand<TL, true> {
+    float pt, jd;
+    TL eta, phi;
+};
+
+// Bytes of one wavefront's list of cap candidates.  Its space first holds the
+// prefix counts of step 3: candidates (low 16 bits) and, extended schema,
+// b-tagged candidates (high 16 bits) before every tile jet.
+template <typename T, int EVPL, bool EXT, bool LK>
+constexpr int list_bytes(int cap) {
+    const int list = cap * static_cast<int>(sizeof(Cand<lds_t<T, EVPL, EXT>, LK>) + (EXT ? 1 : 0));
+    const int pre = (Caps<EVPL, EXT>::JC + 1) * static_cast<int>(sizeof(cpre_t<EXT>));
+    return ((list > pre ? list : pre) + 15) & ~15;
+}
 
 // One wavefront's LDS.  The selected muons and (extended schema) electrons
 // share one pair of arrays in the content's own type, the electrons from
@@ -484,31 +518,14 @@ using cpre_t = std::conditional_t<P, uint32_t, uint16_t>;
 template <typename T, int EVPL, bool EXT, bool LK, bool MS>
 struct WaveLds {
     using C = Caps<EVPL, EXT>;
-    // eta and phi in LDS: the content's own type in the extended schema at one
-    // event per lane (LDS is what limits its wavefronts), else float32
-    // (float16 copies would take registers beside the values of the cuts)
-    using TL = std::conditional_t<EXT && EVPL == 1, T, float>;
+    using TL = lds_t<T, EVPL, EXT>;
     // selected muons, compacted in tile order (+2 padding), then (EXT) the
     // selected electrons likewise from index EO
     TL seta[C::MC + 2 + (EXT ? C::EC + 2 : 0)], sphi[C::MC + 2 + (EXT ? C::EC + 2 : 0)];
     // jets of the events that can pass, as bits; first candidate of each
     // such event in the dense list, as bits
-    uint64_t em[16 + C::JK];  // (JK + SW <= JK + 12 words; the second kind is read 32 lanes wide)
+    uint64_t em[16 + C::JK];  // (JK words of either kind; the second is read 32 lanes wide)
     static constexpr int SM = C::JK;  // the second kind starts here
-    union {
-        // candidates (low 16 bits) and (EXT) b-tagged candidates (high 16
-        // bits) before tile jet j
-        cpre_t<EXT> cpre[C::JC + 1];
-        struct {
-            // the dense candidates in tile order: pt until the cone test,
-            // then NaN for a removed one (with one scale and jet_pt >= 0:
-            // pt * s, +0 for a removed one), eta, phi, energy shift, b-tag
-            float pt[C::CAP];
-            TL eta[C::CAP], phi[C::CAP];
-            float jd[LK ? C::CAP : 1];
-            uint8_t bt[EXT ? C::CAP : 1];
-        } d;
-    };
     union {
         struct {  // steps 2-3: selected leptons before lepton m
             float ssf[LK ? C::MC : 1];  // LK: selected muons' pt, then their scale factors
@@ -522,8 +539,8 @@ struct WaveLds {
         } r;
         struct {  // step 5, several scales: the listed events, candidate
                   // range (first | end << 16) and weight
-            uint32_t evjr[C::TW];
-            float evw[C::TW];
+            uint32_t evjr[MS ? C::TW : 1];
+            float evw[MS ? C::TW : 1];
         } w;
     } u;
 };
@@ -573,12 +590,12 @@ constexpr int kG = 4;
 // any jet is selected; with JM the factor differs per jet and the maximum is
 // taken per scale.  Branch-free, two jets per step (both LDS reads in
 // flight).
-template <int G, bool EXT, bool JM, typename WL>
-__device__ __forceinline__ void walk_jets(const WL &L, int j0, int j1, const float (&sc)[G], float jet_pt,
+template <int G, bool EXT, bool JM, typename CT>
+__device__ __forceinline__ void walk_jets(const CT *C, const uint8_t *bt, int j0, int j1, const float (&sc)[G], float jet_pt,
                                           float (&ht)[G], float (&lead)[G], int (&nj)[G], int (&nb)[G]) {
     float pmax = -INFINITY;
     // selected jets (low 16 bits) and selected b-tagged jets (high 16 bits)
-    // in one counter per scale: a range holds at most CAP < 2^16 jets
+    // in one counter per scale: a range holds at most JC < 2^16 jets
     uint32_t cnt[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -602,13 +619,21 @@ __device__ __forceinline__ void walk_jets(const WL &L, int j0, int j1, const flo
     };
     int k = j0;
     for (; k + 2 <= j1; k += 2) {
-        const float p0 = L.d.pt[k], p1 = L.d.pt[k + 1];
-        const float d0 = JM ? L.d.jd[k] : 0.0f, d1 = JM ? L.d.jd[k + 1] : 0.0f;
-        const int b0 = EXT ? L.d.bt[k] : 0, b1 = EXT ? L.d.bt[k + 1] : 0;
+        const float p0 = C[k].pt, p1 = C[k + 1].pt;
+        float d0 = 0.0f, d1 = 0.0f;
+        if constexpr (JM) {
+            d0 = C[k].jd;
+            d1 = C[k + 1].jd;
+        }
+        const int b0 = EXT ? bt[k] : 0, b1 = EXT ? bt[k + 1] : 0;
         step(p0, d0, b0);
         step(p1, d1, b1);
     }
-    if (k < j1) step(L.d.pt[k], JM ? L.d.jd[k] : 0.0f, EXT ? static_cast<int>(L.d.bt[k]) : 0);
+    if (k < j1) {
+        float d = 0.0f;
+        if constexpr (JM) d = C[k].jd;
+        step(C[k].pt, d, EXT ? static_cast<int>(bt[k]) : 0);
+    }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         nj[g] = static_cast<int>(cnt[g] & 0xffffu);
@@ -624,8 +649,8 @@ __device__ __forceinline__ void walk_jets(const WL &L, int j0, int j1, const flo
 // positive values unchanged, so summing every stored value keeps the sum
 // order of the definition.  The b-tag flag is stored already ANDed with the
 // selection.
-template <bool EXT, typename WL>
-__device__ __forceinline__ void walk_selected(const WL &L, int j0, int j1, float &ht, float &lead, int &nj,
+template <bool EXT, typename CT>
+__device__ __forceinline__ void walk_selected(const CT *C, const uint8_t *bt, int j0, int j1, float &ht, float &lead, int &nj,
                                               int &nb) {
     float h = 0.0f, m = 0.0f;
     int n = 0, b = 0;
@@ -637,12 +662,12 @@ __device__ __forceinline__ void walk_selected(const WL &L, int j0, int j1, float
     };
     int k = j0;
     for (; k + 2 <= j1; k += 2) {
-        const float x0 = L.d.pt[k], x1 = L.d.pt[k + 1];
-        const int b0 = EXT ? L.d.bt[k] : 0, b1 = EXT ? L.d.bt[k + 1] : 0;
+        const float x0 = C[k].pt, x1 = C[k + 1].pt;
+        const int b0 = EXT ? bt[k] : 0, b1 = EXT ? bt[k + 1] : 0;
         step(x0, b0);
         step(x1, b1);
     }
-    if (k < j1) step(L.d.pt[k], EXT ? static_cast<int>(L.d.bt[k]) : 0);
+    if (k < j1) step(C[k].pt, EXT ? static_cast<int>(bt[k]) : 0);
     ht = h;
     nj = n;
     nb = b;
@@ -747,19 +772,25 @@ __device__ __forceinline__ int compact(const bool (&sel)[K], const float (&eta)[
 // interpolated table (jes_mode 1) -- and the sums of squared weights; a
 // query without lookups runs exactly as in the kernels without LK.
 template <typename T, bool EXT, int WAVES, int EVPL, bool LDSH, bool MS, bool DBG, bool LK>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(MS ? 2 : (EXT || LK ? 4 : 6)))) void
-pipeline_kernel(PipeArgs P) {
+__global__ __launch_bounds__(64 * WAVES)
+    __attribute__((amdgpu_waves_per_eu(MS || (EVPL == 2 && EXT) ? 2 : (EXT || LK || EVPL == 2 ? 4 : 6)))) void
+    pipeline_kernel(PipeArgs P) {
     using C = Caps<EVPL, EXT>;
-    constexpr int TW = C::TW, JK = C::JK, MK = C::MK, EK = C::EK, CAP = C::CAP;
+    constexpr int TW = C::TW, JK = C::JK, MK = C::MK, EK = C::EK;
     __shared__ WaveLds<T, EVPL, EXT, LK, MS> wl[WAVES];
     using TL = typename WaveLds<T, EVPL, EXT, LK, MS>::TL;
-    // per workgroup: [sumw | sumw2 (LK) | counts (u32) | edges | scales]
+    // per workgroup: [sumw | sumw2 (LK) | counts (u32) | edges | scales | candidate lists]
     extern __shared__ double dyn[];
 
     const int tid = threadIdx.x;
     int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto &L = wl[wave];
+    // this wavefront's list, its b-tags, and the prefix counts in its space
+    const int cap = P.list_cap;
+    auto *cand = reinterpret_cast<Cand<TL, LK> *>(reinterpret_cast<char *>(dyn) + P.list_at + wave * P.list_bytes);
+    uint8_t *cbt = reinterpret_cast<uint8_t *>(cand + cap);
+    auto *cpre = reinterpret_cast<cpre_t<EXT> *>(cand);
 
     double *sw_s = dyn;
     double *sw2_s = dyn + (LDSH ? P.ds_slots : 0);
@@ -1100,12 +1131,12 @@ pipeline_kernel(PipeArgs P) {
                             before |= static_cast<uint32_t>(bits_below(tg, runt)) << 16;
                             runt += __popcll(tg);
                         }
-                        L.cpre[j] = static_cast<cpre_t<EXT>>(before);
+                        cpre[j] = static_cast<cpre_t<EXT>>(before);
                     }
-                    L.cpre[C::JC] = static_cast<cpre_t<EXT>>(static_cast<uint32_t>(runc) |
+                    cpre[C::JC] = static_cast<cpre_t<EXT>>(static_cast<uint32_t>(runc) |
                                                              (EXT ? static_cast<uint32_t>(runt) << 16 : 0u));
                 }
-                if (lane < 2 * (JK + C::SW)) reinterpret_cast<uint32_t *>(L.em)[lane] = 0u;
+                if (lane < 4 * JK) reinterpret_cast<uint32_t *>(L.em)[lane] = 0u;
                 wave_sync();
                 // each event's selected-lepton ranges (first | count << 16) and
                 // (below) its weight
@@ -1134,7 +1165,7 @@ pipeline_kernel(PipeArgs P) {
                 bool some = false;
 #pragma unroll
                 for (int r = 0; r < EVPL; ++r) {
-                    const uint32_t cw0 = L.cpre[jb[r]], cw1 = L.cpre[je[r]];
+                    const uint32_t cw0 = cpre[jb[r]], cw1 = cpre[je[r]];
                     const int nc = static_cast<int>((cw1 & 0xffffu) - (cw0 & 0xffffu));
                     elig[r] = (lane + 64 * r < ne) & (nmu[r] >= min_mu) & (je[r] - jb[r] >= min_jet) &
                               (lane + 64 * r >= wlo);
@@ -1180,14 +1211,14 @@ pipeline_kernel(PipeArgs P) {
                     }
                 }
                 int whi = TW;
-                if (total > CAP) {
+                if (total > cap) {
                     // the events up to the first that does not fit (every event
-                    // has at most CAP jets, so the first one always fits)
+                    // lists at most cap, so the first one always fits)
                     int fit_total = total;
                     some = false;
 #pragma unroll
                     for (int r = EVPL - 1; r >= 0; --r) {
-                        const bool fit = start[r] + cnt[r] <= CAP;
+                        const bool fit = start[r] + cnt[r] <= cap;
                         const int nf = __popcll(__ballot(fit));
                         if (nf < 64) {
                             whi = 64 * r + nf;
@@ -1246,10 +1277,10 @@ pipeline_kernel(PipeArgs P) {
                         const uint64_t d = okm[k] & lane_u64(ew, 2 * k);
                         const int dst = bits_below(d, run);
                         if (__builtin_amdgcn_inverse_ballot_w64(d)) {
-                            L.d.pt[dst] = jpt[k] * f;
-                            L.d.eta[dst] = static_cast<TL>(jeta[k]);
-                            L.d.phi[dst] = static_cast<TL>(jphi[k]);
-                            if (EXT) L.d.bt[EXT ? dst : 0] = (has_bt & (jbt[EXT ? k : 0] > btag)) ? 1 : 0;
+                            cand[dst].pt = jpt[k] * f;
+                            cand[dst].eta = static_cast<TL>(jeta[k]);
+                            cand[dst].phi = static_cast<TL>(jphi[k]);
+                            if (EXT) cbt[dst] = (has_bt & (jbt[EXT ? k : 0] > btag)) ? 1 : 0;
                         }
                         run += __popcll(d);
                     }
@@ -1279,10 +1310,19 @@ pipeline_kernel(PipeArgs P) {
                             const int p = p0 + 64 * b + lane;
                             wm[b] = L.u.r.mu[o];
                             we[b] = EXT ? L.u.r.el[EXT ? o : 0] : 0u;
-                            eta[b] = ldf(L.d.eta, p);
-                            phi[b] = ldf(L.d.phi, p);
-                            pt[b] = LK ? L.d.pt[p] : 0.0f;
+                            eta[b] = static_cast<float>(cand[p].eta);
+                            phi[b] = static_cast<float>(cand[p].phi);
+                            pt[b] = LK ? cand[p].pt : 0.0f;
                             dsh[b] = 0.0f;
+                        }
+                        if constexpr (LK) {  // (before the leptons are read: fewer registers live)
+                            if (shift)
+                                on_tables([&](const float *E) {
+                                    if (Q.jseg >= 0)
+                                        jes_lut_n<CB>(Q, E, pt, eta, dsh);
+                                    else
+                                        jes_shift_n<CB>(lk_axes(Q, E), E, Q.jd, pt, eta, dsh);
+                                });
                         }
                         int s0[CB], nm_[CB], ofe[CB], nlep[CB];
                         float e0[CB], f0[CB], e1[CB], f1[CB];
@@ -1298,15 +1338,6 @@ pipeline_kernel(PipeArgs P) {
                             f0[b] = ldf(L.sphi, i0);
                             e1[b] = ldf(L.seta, i1);
                             f1[b] = ldf(L.sphi, i1);
-                        }
-                        if constexpr (LK) {
-                            if (shift)
-                                on_tables([&](const float *E) {
-                                    if (Q.jseg >= 0)
-                                        jes_lut_n<CB>(Q, E, pt, eta, dsh);
-                                    else
-                                        jes_shift_n<CB>(lk_axes(Q, E), E, Q.jd, pt, eta, dsh);
-                                });
                         }
 #pragma unroll
                         for (int b = 0; b < CB; ++b) {
@@ -1336,19 +1367,19 @@ pipeline_kernel(PipeArgs P) {
                                     // one scale s (= smax): the jet's energy pt * (1 + s * d)
                                     const float x = pt[b] * (1.0f + smax * dsh[b]);
                                     const bool sel = !hit & (x > jet_pt);
-                                    L.d.pt[p] = sel ? x : 0.0f;
-                                    if (EXT && !sel) L.d.bt[EXT ? p : 0] = 0;
+                                    cand[p].pt = sel ? x : 0.0f;
+                                    if (EXT && !sel) cbt[p] = 0;
                                 } else {
                                     // (an energy not above jet_pt at any scale is
                                     // removed too: the records count it so)
                                     if (DBG && jet_pt >= 0.0f)
                                         hit |= !(shifted_pt_bound(pt[b], dsh[b], Q.smin, smax) > jet_pt);
-                                    L.d.jd[LK ? p : 0] = dsh[b];
-                                    if (hit) L.d.pt[p] = __builtin_nanf("");
+                                    if constexpr (LK) cand[p].jd = dsh[b];
+                                    if (hit) cand[p].pt = __builtin_nanf("");
                                 }
                             } else if (live & hit) {
-                                L.d.pt[p] = zsel ? 0.0f : __builtin_nanf("");
-                                if (EXT) L.d.bt[EXT ? p : 0] = 0;
+                                cand[p].pt = zsel ? 0.0f : __builtin_nanf("");
+                                if (EXT) cbt[p] = 0;
                             }
                         }
                     };
@@ -1376,9 +1407,9 @@ pipeline_kernel(PipeArgs P) {
                                 float ht[1], lead[1];
                                 int njs[1], nbt[1];
                                 if (shift)
-                                    walk_jets<1, EXT, true>(L, start[r], start[r] + cnt[r], sc, jet_pt, ht, lead, njs, nbt);
+                                    walk_jets<1, EXT, LK>(cand, cbt, start[r], start[r] + cnt[r], sc, jet_pt, ht, lead, njs, nbt);
                                 else
-                                    walk_jets<1, EXT, false>(L, start[r], start[r] + cnt[r], sc, jet_pt, ht, lead, njs, nbt);
+                                    walk_jets<1, EXT, false>(cand, cbt, start[r], start[r] + cnt[r], sc, jet_pt, ht, lead, njs, nbt);
                                 const bool pass = njs[0] >= min_jet && nbt[0] >= min_b;
                                 if (DBG)
                                     *rec_at(P, N.scale0 + v, D.ev0 + e0 + lane + 64 * r) = hepk_event_record{
@@ -1408,11 +1439,11 @@ pipeline_kernel(PipeArgs P) {
                             int njs[1], nbt[1];
                             const int k0 = start[r], k1 = k0 + cnt[r];  // (empty unless elig)
                             if (zsel)
-                                walk_selected<EXT>(L, k0, k1, ht[0], lead[0], njs[0], nbt[0]);
+                                walk_selected<EXT>(cand, cbt, k0, k1, ht[0], lead[0], njs[0], nbt[0]);
                             else if (shift)
-                                walk_jets<1, EXT, true>(L, k0, k1, sc, jet_pt, ht, lead, njs, nbt);
+                                walk_jets<1, EXT, LK>(cand, cbt, k0, k1, sc, jet_pt, ht, lead, njs, nbt);
                             else
-                                walk_jets<1, EXT, false>(L, k0, k1, sc, jet_pt, ht, lead, njs, nbt);
+                                walk_jets<1, EXT, false>(cand, cbt, k0, k1, sc, jet_pt, ht, lead, njs, nbt);
                             const bool pass[1] = {elig[r] && njs[0] >= min_jet && nbt[0] >= min_b};
                             if (DBG && elig[r])
                                 *rec_at(P, Q.scale0, D.ev0 + e0 + lane + 64 * r) = hepk_event_record{
@@ -1439,9 +1470,9 @@ pipeline_kernel(PipeArgs P) {
                                 // b-tagged jets at the largest scale apart
                                 int kj = 0, kb = 0;
                                 for (int k = k0; k < k1; ++k) {
-                                    const bool kept = L.d.pt[k] == L.d.pt[k];
+                                    const bool kept = cand[k].pt == cand[k].pt;
                                     kj += kept ? 1 : 0;
-                                    kb += (EXT && kept) ? L.d.bt[EXT ? k : 0] : 0;
+                                    kb += (EXT && kept) ? cbt[k] : 0;
                                 }
                                 in = kj >= min_jet && kb >= min_b;
                                 for (int v = 0; v < Q.n_scale && !in; ++v) {
@@ -1457,7 +1488,7 @@ pipeline_kernel(PipeArgs P) {
                             const int at = bits_below(bal, nel);
                             if (in) {
                                 // candidate range: first in bits 0-9, end in bits
-                                // 16-25 (both at most CAP < 2^10); DBG kernels
+                                // 16-25 (both at most JC < 2^10); DBG kernels
                                 // keep the event's place in the tile in the bits
                                 // between
                                 const uint32_t ev = static_cast<uint32_t>(lane + 64 * r);
@@ -1484,9 +1515,9 @@ pipeline_kernel(PipeArgs P) {
                             int njs[kG], nbt[kG];
                             const int wj0 = static_cast<int>(jr & 0x3ffu), wj1 = static_cast<int>((jr >> 16) & 0x3ffu);
                             if (shift)
-                                walk_jets<kG, EXT, true>(L, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
+                                walk_jets<kG, EXT, LK>(cand, cbt, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
                             else
-                                walk_jets<kG, EXT, false>(L, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
+                                walk_jets<kG, EXT, false>(cand, cbt, wj0, wj1, sc, jet_pt, ht, lead, njs, nbt);
                             bool pass[kG], any = false;
 #pragma unroll
                             for (int u = 0; u < kG; ++u) {
@@ -1587,7 +1618,7 @@ pipeline_kernel(PipeArgs P) {
             bool direct = over;
 #pragma unroll
             for (int i = 0; i < EVPL; ++i) {
-                uint64_t lb = __ballot((lane + 64 * i < n) & (R.j1[i] - R.j0[i] > static_cast<uint32_t>(CAP)));
+                uint64_t lb = __ballot((lane + 64 * i < n) & (R.j1[i] - R.j0[i] > static_cast<uint32_t>(cap)));
                 for (; lb != 0 && !over; lb &= lb - 1) {
                     const int l = __builtin_ctzll(lb);
                     const int ja = static_cast<int>(__builtin_amdgcn_readlane(R.j0[i], l) - static_cast<uint32_t>(B.J0));
@@ -1602,7 +1633,7 @@ pipeline_kernel(PipeArgs P) {
                             nc += __popcll(__ballot((j >= ja) & (j < jz) & (fabsf(raw_f<T>(R.jeta[k])) < Q.jet_abseta) &
                                                     (raw_f<T>(R.jpt[k]) >= Q.ptmin)));
                         }
-                        beyond |= (nc > CAP) & (Q.active != 0);
+                        beyond |= (nc > cap) & (Q.active != 0);
                     }
                     if (beyond) {
                         direct = 64 * i + l == 0;
@@ -1677,10 +1708,10 @@ static KernelFn pick_h(bool ldsh) {
 template <typename T, bool EXT, bool MS, bool DBG, bool LK>
 static KernelFn pick_shape(int block, int evpt, bool ldsh) {
     if (block == 1024) return pick_h<T, EXT, 16, 1, MS, DBG, LK>(ldsh);  // one event per thread only
-    if (LK) return block == 512 ? pick_h<T, EXT, 8, 1, MS, DBG, LK>(ldsh) : pick_h<T, EXT, 4, 1, MS, DBG, LK>(ldsh);
-    if (block == 512)
-        return evpt == 2 ? pick_h<T, EXT, 8, 2, MS, DBG, LK>(ldsh) : pick_h<T, EXT, 8, 1, MS, DBG, LK>(ldsh);
-    return evpt == 2 ? pick_h<T, EXT, 4, 2, MS, DBG, LK>(ldsh) : pick_h<T, EXT, 4, 1, MS, DBG, LK>(ldsh);
+    if constexpr (!LK) {
+        if (evpt == 2) return block == 512 ? pick_h<T, EXT, 8, 2, MS, DBG, LK>(ldsh) : pick_h<T, EXT, 4, 2, MS, DBG, LK>(ldsh);
+    }
+    return block == 512 ? pick_h<T, EXT, 8, 1, MS, DBG, LK>(ldsh) : pick_h<T, EXT, 4, 1, MS, DBG, LK>(ldsh);
 }
 
 // The kernel for a launch shape; each (MS, DBG, LK) triple is instantiated

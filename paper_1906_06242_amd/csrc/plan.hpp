@@ -21,7 +21,9 @@ struct hepk_plan_s {
     bool dbg_ok = false;               // record kernels have the product kernels' LDS
     std::vector<int64_t> ev_pre;       // n_ds + 1: events of the datasets before each
     size_t lds_static_lds = 0, lds_static_glob = 0;  // static LDS of the two kernels
-    size_t lds_max = 0;                              // the device's LDS per workgroup
+    size_t lds_max = 0, lds_cu = 0;                  // the device's LDS per workgroup and per CU
+    int regs_lds = 1, regs_glob = 1;                 // workgroups per CU the two kernels' registers allow
+    int list_most = 0;                               // longest candidate list
     hepk::PipeArgs args{};             // table pointers; chunk range and histograms set per launch
     std::vector<int64_t> tile_pre;     // n_ds + 1: tiles of the datasets before each (chunk d = dataset d)
     int64_t ds_block = 0;              // histogram slots per dataset block
