@@ -372,23 +372,27 @@ static void lk_place(QDev &o, const hepk_query &Q, std::vector<float> &tab) {
         o.jd = put(Q.jes_delta, static_cast<size_t>(Q.jes_n_eta) * Q.jes_n_pt);
         axis(Q.jes_eta_edges, Q.jes_n_eta, o.jr_lo, o.jr_hi, o.jr_iw);
         axis(Q.jes_pt_edges, Q.jes_n_pt, o.jc_lo, o.jc_hi, o.jc_iw);
-        // the same table as buckets and segments, where the whole edge table
-        // still goes to LDS with them
-        const int nr = Q.jes_n_eta, nc = Q.jes_n_pt;
-        std::vector<float> with = tab, centres(nc);
-        for (int i = 0; i < nc; ++i) centres[i] = bin_centre(Q.jes_pt_edges[i], Q.jes_pt_edges[i + 1]);
-        if (lut_place(o.jlr, std::vector<float>(Q.jes_eta_edges, Q.jes_eta_edges + nr + 1), with) &&
-            lut_place(o.jlc, centres, with) &&
-            (with.size() + 4 * static_cast<size_t>(nr) * (nc + 1)) * sizeof(float) <= kMaxLdsLookupBytes) {
-            o.jseg = static_cast<int32_t>(with.size());
-            for (int r = 0; r < nr; ++r)
-                for (int i = 0; i <= nc; ++i) {
-                    const Segment g = make_segment(centres.data(), Q.jes_delta + static_cast<int64_t>(r) * nc, nc, i);
-                    with.insert(with.end(), {g.m0, g.v0, g.slope, 0.0f});
-                }
-            tab.swap(with);
-        }
     }
+}
+
+// Appends the bucket tables and segments of the query's shift table, if they
+// fit an edge table of `most` bytes with it.
+static void lk_place_segments(QDev &o, const hepk_query &Q, std::vector<float> &tab, size_t most) {
+    if (Q.jes_mode != 1) return;
+    const int nr = Q.jes_n_eta, nc = Q.jes_n_pt;
+    std::vector<float> with = tab, centres(nc);
+    for (int i = 0; i < nc; ++i) centres[i] = bin_centre(Q.jes_pt_edges[i], Q.jes_pt_edges[i + 1]);
+    if (!lut_place(o.jlr, std::vector<float>(Q.jes_eta_edges, Q.jes_eta_edges + nr + 1), with) ||
+        !lut_place(o.jlc, centres, with) ||
+        (with.size() + 4 * static_cast<size_t>(nr) * (nc + 1)) * sizeof(float) > most)
+        return;
+    o.jseg = static_cast<int32_t>(with.size());
+    for (int r = 0; r < nr; ++r)
+        for (int i = 0; i <= nc; ++i) {
+            const Segment g = make_segment(centres.data(), Q.jes_delta + static_cast<int64_t>(r) * nc, nc, i);
+            with.insert(with.end(), {g.m0, g.v0, g.slope, 0.0f});
+        }
+    tab.swap(with);
 }
 
 Launch make_launch(hepk_plan p, int32_t c0, int32_t c1, double *sumw, uint64_t *counts, hepk_event_record *rec,
@@ -577,10 +581,12 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
     }
     p->ds_block = gacc;
     p->n_slots = p->shared ? gacc : gacc * n_ds;
-    p->n_edges = static_cast<int32_t>(edge_table.size());
-    p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(p->lk ? kMaxLdsLookupBytes : kMaxLdsEdgeBytes);
+    // the segments come after every query's own tables, as far as all of them
+    // still go to LDS together
+    const size_t own_edges = edge_table.size();
+    if (own_edges * sizeof(float) <= static_cast<size_t>(kMaxLdsLookupBytes))
+        for (int i = 0; i < n_query; ++i) lk_place_segments(p->qd[i], q[i], edge_table, kMaxLdsLookupBytes);
     p->n_scales = static_cast<int32_t>(scales.size());
-    p->scales_lds = scales.size() * sizeof(float) <= static_cast<size_t>(kMaxLdsScaleBytes);
     p->tune = t;
     relayout(p);
 
@@ -647,14 +653,23 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
         p->lds_max = static_cast<size_t>(mx);
         p->lds_cu = static_cast<size_t>(std::max(mx, mcu));
         const size_t least_lists = list_lds_bytes(p, list_min(p));
-        // the tables go to LDS only if they fit beside the kernel's own LDS
-        p->edges_lds = static_cast<size_t>(p->n_edges) * sizeof(float) <= static_cast<size_t>(p->lk ? kMaxLdsLookupBytes : kMaxLdsEdgeBytes);
-        p->scales_lds = static_cast<size_t>(p->n_scales) * sizeof(float) <= static_cast<size_t>(kMaxLdsScaleBytes);
-        if (p->lds_static_glob + least_lists + dyn_lds_bytes(p, false) > p->lds_max) p->edges_lds = p->scales_lds = false;
-        // (large lookup tables leave LDS to the histograms when both do not fit)
-        if (p->edges_lds && static_cast<size_t>(p->n_edges) * sizeof(float) > static_cast<size_t>(kMaxLdsEdgeBytes) &&
-            t.hist_mode == 0 && !use_lds_hist(p))
-            p->edges_lds = false;
+        // the tables go to LDS if they are small and fit beside the kernel's
+        // own LDS; in lookup plans the segments, then the tables, leave it to
+        // the histograms where that lets those in (20 shifts, 150 bins over
+        // 2e6 events: tables in HBM 354 us, a smaller workgroup 440, global
+        // histograms 5000)
+        auto place_tables = [&](size_t n, bool lds) {
+            p->n_edges = static_cast<int32_t>(n);
+            p->edges_lds =
+                lds && n * sizeof(float) <= static_cast<size_t>(p->lk ? kMaxLdsLookupBytes : kMaxLdsEdgeBytes);
+            p->scales_lds = static_cast<size_t>(p->n_scales) * sizeof(float) <= static_cast<size_t>(kMaxLdsScaleBytes);
+            if (p->lds_static_glob + least_lists + dyn_lds_bytes(p, false) > p->lds_max)
+                p->edges_lds = p->scales_lds = false;
+            return !p->lk || t.hist_mode != 0 || use_lds_hist(p);
+        };
+        if (!place_tables(edge_table.size(), true) && !place_tables(own_edges, true) &&
+            !place_tables(edge_table.size(), false))
+            place_tables(edge_table.size(), true);
         if (p->lds_static_glob + least_lists + dyn_lds_bytes(p, false) > p->lds_max) {
             set_error("hepk_plan_create: kernel needs %zu bytes of LDS, device has %zu", p->lds_static_glob,
                       p->lds_max);
@@ -663,6 +678,10 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
         if (!default_block || t.hist_mode != 0 || use_lds_hist(p) || t.block == 256) break;
         t.block = t.block == 1024 ? 512 : 256;
         p->tune = t;
+    }
+    if (static_cast<size_t>(p->n_edges) < edge_table.size()) {
+        edge_table.resize(p->n_edges);
+        for (auto &e : p->qd) e.jseg = -1;
     }
     // Workgroups per CU: what the registers allow -- six wavefronts per SIMD
     // at most (only 256-thread workgroups of the base kernel reach a seventh:
