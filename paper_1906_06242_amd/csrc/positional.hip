@@ -11,6 +11,8 @@
 // consecutive events, takes their objects 64 at a time in order, and places
 // the kept ones by a wavefront ballot and prefix count, so both its reads and
 // its writes are contiguous runs.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace hepk {
@@ -110,6 +112,56 @@ struct OsBest {
 // 1: selected, positive; 2: selected, negative; 0: neither
 __device__ __forceinline__ uint32_t os_code(uint32_t m, int32_t q) { return m == 0u ? 0u : (q > 0 ? 1u : (q < 0 ? 2u : 0u)); }
 
+// A pt's place in pT order as an integer: 1 for NaN, above it the numbers
+// ascending, -0 as +0 (0 is left for "no object").
+__device__ __forceinline__ uint32_t os_key(float p) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, p + 0.0f);
+    return p != p ? 1u : ((u & 0x80000000u) ? ~u : u | 0x80000000u);
+}
+
+// Largest v over the wavefront (every lane active).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    auto up = [&](auto ctl, auto rows) {
+        return max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), decltype(ctl)::value,
+                                                                        decltype(rows)::value, 0xf, false)));
+    };
+    using all = std::integral_constant<int, 0xf>;
+    v = up(std::integral_constant<int, 0x111>{}, all{});  // row_shr:1
+    v = up(std::integral_constant<int, 0x112>{}, all{});  // row_shr:2
+    v = up(std::integral_constant<int, 0x114>{}, all{});  // row_shr:4
+    v = up(std::integral_constant<int, 0x118>{}, all{});  // row_shr:8
+    v = up(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});  // row_bcast:15
+    v = up(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});  // row_bcast:31
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+}
+
+// The pair of one event of n objects by the whole wavefront: get(i, code, pt)
+// reads object i.  The best object of a sign is the lowest index among the
+// largest keys.
+struct OsPair {
+    int64_t p, n;  // -1: none
+};
+template <typename G>
+__device__ __forceinline__ OsPair os_pair(int lane, int64_t n, G &&get) {
+    uint32_t kp = 0, kn = 0, ip = 0, in = 0;
+#pragma unroll 1
+    for (int64_t i = lane; i < n; i += 64) {
+        uint32_t code;
+        float pt;
+        get(i, code, pt);
+        const uint32_t k = os_key(pt);
+        const bool up = (code == 1u) & (k > kp), dn = (code == 2u) & (k > kn);
+        kp = up ? k : kp;
+        ip = up ? static_cast<uint32_t>(i) : ip;
+        kn = dn ? k : kn;
+        in = dn ? static_cast<uint32_t>(i) : in;
+    }
+    const uint32_t mp = wave_max(kp), mn = wave_max(kn);
+    const uint32_t bp = ~wave_max(kp == mp ? ~ip : 0u), bn = ~wave_max(kn == mn ? ~in : 0u);
+    if (mp == 0u || mn == 0u) return {-1, -1};
+    return {static_cast<int64_t>(bp), static_cast<int64_t>(bn)};
+}
+
 // Each wavefront takes tiles of 64 consecutive events: the tile's objects as
 // coalesced buffer loads over exactly its range, waited for once, staged in
 // LDS with their code; one lane per event walks its objects there and marks
@@ -117,9 +169,12 @@ __device__ __forceinline__ uint32_t os_code(uint32_t m, int32_t q) { return m ==
 // per event reading its objects itself took 24 gathers of 64 scattered
 // addresses per tile and was bound by their address rate: 76 -> 37 us on
 // 7.5e6 muons in 5e6 events (115 MB; floor 17 us).  Tiles with more objects
-// than the staging holds run in parts; a single event beyond it goes one
-// lane, straight from HBM.
-constexpr int kOsSlots = 8;  // objects per lane staged for one tile
+// than the staging holds run in parts.  Parts of few events, which would leave
+// most lanes idle, are taken event by event by the whole wavefront, straight
+// from HBM (events of 300 objects 2500 -> 180 us per 1.5e7 objects, of 2000
+// 20 -> 0.87 ms per 2e7).
+constexpr int kOsSlots = 8;   // objects per lane staged for one tile
+constexpr int kOsFew = 8;     // events of a part that go one by one
 
 template <typename T>
 __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__restrict__ off, int64_t n_events,
@@ -151,27 +206,15 @@ __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__rest
                 e1 = e0 + (e1 - e0 + 1) / 2;
                 B = as_const(off)[e1];
             }
-            if (B - A > 64 * kOsSlots) {
-                if (lane == 0) {
-                    int64_t bp = -1, bn = -1;
-                    float pp = 0.0f, pn = 0.0f;
-                    for (int64_t i = A; i < B; ++i) {
-                        out[i] = 0;
-                        const uint32_t c = os_code(om ? om[i] : 1u, q[i]);
-                        const float p = ldf(pt, i);
-                        if (c == 1u && (bp < 0 || p > pp || (pp != pp && p == p))) {
-                            bp = i;
-                            pp = p;
-                        }
-                        if (c == 2u && (bn < 0 || p > pn || (pn != pn && p == p))) {
-                            bn = i;
-                            pn = p;
-                        }
-                    }
-                    if (bp >= 0 && bn >= 0) {
-                        out[bp] = 1;
-                        out[bn] = 1;
-                    }
+            if (__builtin_expect(e1 - e0 <= kOsFew, 0)) {
+                for (int64_t e = e0; e < e1; ++e) {
+                    const int64_t a0 = as_const(off)[e], m = as_const(off)[e + 1] - a0;
+                    const OsPair b = os_pair(lane, m, [&](int64_t i, uint32_t &code, float &p) {
+                        code = os_code(om ? om[a0 + i] : 1u, q[a0 + i]);
+                        p = ldf(pt, a0 + i);
+                    });
+#pragma unroll 1
+                    for (int64_t i = lane; i < m; i += 64) out[a0 + i] = (b.p >= 0 && (i == b.p || i == b.n)) ? 1 : 0;
                 }
                 e0 = e1;
                 continue;
