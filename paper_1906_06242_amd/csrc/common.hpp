@@ -206,6 +206,20 @@ __device__ __forceinline__ int hist_slot_lohi(float x, const float *E, int nbins
     return (x < E[s - 1] || x >= E[s]) ? bin_search(E, nbins, x) : s;
 }
 
+// Largest v over the wavefront (every lane active).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#define HEPK_DPP_MAX(ctl, rows) \
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), ctl, rows, 0xf, false)))
+    HEPK_DPP_MAX(0x111, 0xf);  // row_shr:1
+    HEPK_DPP_MAX(0x112, 0xf);  // row_shr:2
+    HEPK_DPP_MAX(0x114, 0xf);  // row_shr:4
+    HEPK_DPP_MAX(0x118, 0xf);  // row_shr:8
+    HEPK_DPP_MAX(0x142, 0xa);  // row_bcast:15
+    HEPK_DPP_MAX(0x143, 0xc);  // row_bcast:31
+#undef HEPK_DPP_MAX
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+}
+
 __device__ __forceinline__ void atomic_add_f64(double *p, double v) {
     unsafeAtomicAdd(p, v);  // global_atomic_add_f64 / ds_add_f64 on gfx950
 }

@@ -11,8 +11,6 @@
 // consecutive events, takes their objects 64 at a time in order, and places
 // the kept ones by a wavefront ballot and prefix count, so both its reads and
 // its writes are contiguous runs.
-#include <type_traits>
-
 #include "common.hpp"
 
 namespace hepk {
@@ -117,22 +115,6 @@ __device__ __forceinline__ uint32_t os_code(uint32_t m, int32_t q) { return m ==
 __device__ __forceinline__ uint32_t os_key(float p) {
     const uint32_t u = __builtin_bit_cast(uint32_t, p + 0.0f);
     return p != p ? 1u : ((u & 0x80000000u) ? ~u : u | 0x80000000u);
-}
-
-// Largest v over the wavefront (every lane active).
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-    auto up = [&](auto ctl, auto rows) {
-        return max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), decltype(ctl)::value,
-                                                                        decltype(rows)::value, 0xf, false)));
-    };
-    using all = std::integral_constant<int, 0xf>;
-    v = up(std::integral_constant<int, 0x111>{}, all{});  // row_shr:1
-    v = up(std::integral_constant<int, 0x112>{}, all{});  // row_shr:2
-    v = up(std::integral_constant<int, 0x114>{}, all{});  // row_shr:4
-    v = up(std::integral_constant<int, 0x118>{}, all{});  // row_shr:8
-    v = up(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});  // row_bcast:15
-    v = up(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});  // row_bcast:31
-    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
 }
 
 // The pair of one event of n objects by the whole wavefront: get(i, code, pt)

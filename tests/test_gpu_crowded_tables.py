@@ -65,3 +65,16 @@ def test_two_dimensions(rows, cols):
     pt, eta = values(ce, 4), values(re, 5)
     with np.errstate(invalid="ignore"):
         same(H.jes_delta(dev(pt), dev(eta), dev(re), dev(ce), dev(d)), ref.jes_delta(pt, eta, re, ce, d))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("cols", [1, 2, 15, 16])
+@pytest.mark.parametrize("n", [(1 << 21) - 1, 1 << 21, (1 << 21) + (1 << 19) - 1, (1 << 21) + (1 << 19)])
+def test_route_limits(n, cols, dtype):
+    """Shifts on either side of the sizes from which the bucket tables are taken."""
+    print("bucket table limits", n, cols, dtype, flush=True)
+    rng = np.random.default_rng(n + cols)
+    re, ce = np.linspace(0, 5, 5).astype(F), np.geomspace(20, 1000, cols + 1).astype(F)
+    d = rng.normal(0, 0.05, (4, cols)).astype(F)
+    pt, eta = (rng.uniform(a, b, n).astype(np.float16 if dtype == "f16" else F) for a, b in ((0, 1100), (-6, 6)))
+    same(H.jes_delta(dev(pt), dev(eta), dev(re), dev(ce), dev(d)), ref.jes_delta(pt, eta, re, ce, d))
