@@ -434,7 +434,12 @@ static void launch_match(int grid, hipStream_t s, const int64_t *off_a, const vo
                          uint8_t *clean) {
     const T *ea = static_cast<const T *>(eta_a), *pa = static_cast<const T *>(phi_a);
     const T *eb = static_cast<const T *>(eta_b), *pb = static_cast<const T *>(phi_b);
-    if (!min_dr2 && !idx_b)
+    // Unmasked float32 objects, where there is nothing to compact and the loads
+    // are twice as long, are no faster there (3e6 events: 43 us both of 5 a and
+    // 1.5 b objects, 26 against 24 of 1 and 0.2; 1e6 events of 10 and 3, beyond
+    // the staging, 189 against 177; masked or float16 10-30% faster).
+    const bool plain = sizeof(T) == 4 && !mask_a && !mask_b;
+    if (!min_dr2 && !idx_b && !plain)
         match_clean_kernel<T><<<grid, 64 * MW, 0, s>>>(off_a, ea, pa, mask_a, off_b, eb, pb, mask_b, n_events, thr2,
                                                        clean);
     else
