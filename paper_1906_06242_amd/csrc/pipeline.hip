@@ -69,8 +69,8 @@ static size_t list_lds_bytes(hepk_plan p, int cap) {
 }
 
 static int list_min(hepk_plan p) {
-    if (p->tune.ev_per_thread == 2) return p->ext ? Caps<2, true>::CAP_MIN : Caps<2, false>::CAP_MIN;
-    return p->ext ? Caps<1, true>::CAP_MIN : Caps<1, false>::CAP_MIN;
+    if (p->tune.ev_per_thread == 2) return p->ext ? Caps<2, true, false>::CAP_MIN : Caps<2, false, false>::CAP_MIN;
+    return p->ext ? Caps<1, true, false>::CAP_MIN : Caps<1, false, false>::CAP_MIN;
 }
 
 // Dynamic LDS of a workgroup before its candidate lists (16-byte aligned).
@@ -685,14 +685,17 @@ int plan_build(const hepk_dataset *ds, int32_t n_ds, const hepk_query *q, int32_
     }
     // Workgroups per CU: what the registers allow -- six wavefronts per SIMD
     // at most (only 256-thread workgroups of the base kernel reach a seventh:
-    // 5e6 events 138 us with seven, 117 with six) -- and the LDS with the
-    // smallest lists; longer lists must not cost a workgroup.
+    // 5e6 events 138 us with seven, 117 with six), two in the extended schema
+    // at two events per lane (three 256-thread workgroups of 53 KB are counted
+    // as fitting: 3e6 events 149 us with them, 123 with two) -- and the LDS
+    // with the smallest lists; longer lists must not cost a workgroup.
+    const int most_waves = p->ext && t.ev_per_thread == 2 ? 8 : 24;
     auto per_cu_at = [&](bool ldsh, size_t lds) {
         int n = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
                 &n, reinterpret_cast<const void *>(ldsh ? p->fn_lds : p->fn_glob), t.block, lds) != hipSuccess)
             n = 1;
-        return std::max(1, std::min(n, 24 / (t.block / 64)));
+        return std::max(1, std::min(n, most_waves / (t.block / 64)));
     };
     p->regs_lds = per_cu_at(true, 0);
     p->regs_glob = per_cu_at(false, 0);

@@ -458,7 +458,7 @@ __device__ __forceinline__ void event_direct(const PipeArgs &P, const DsDev &D, 
     }
 }
 
-template <int EVPL, bool EXT>
+template <int EVPL, bool EXT, bool LK>
 struct Caps {
     static constexpr int TW = 64 * EVPL;             // events per wavefront tile
     // (Seven jet slots where six hold the paper's five per event with 3.5 sigma
@@ -466,8 +466,15 @@ struct Caps {
     // against 50; at five they would be 2% faster.)
     static constexpr int JK = 6 * EVPL + 1;          // jet slots per lane
     static constexpr int MK = 2 * EVPL;              // muon slots per lane
+    // One more slot of muons that no register holds: read per query in the
+    // tiles that have so many (at two muons per event half of the tiles do).
+    // 3e6 events of 2.3 muons, those tiles split in two / with the slot: base
+    // 109 / 77 us, eight queries 516 / 356, extended 165 / 108.  A third
+    // register slot would leave five wavefronts per SIMD instead of six.  The
+    // lookup kernels, whose LDS is full, split.
+    static constexpr int MX = LK ? 0 : 1;
     static constexpr int EK = EXT ? 2 * EVPL : 1;    // electron slots per lane
-    static constexpr int JC = 64 * JK, MC = 64 * MK, EC = 64 * EK;
+    static constexpr int JC = 64 * JK, MC = 64 * (MK + MX), EC = 64 * EK;
     // The least the dense list of candidates holds (a tile with more takes
     // its events in several passes, each as many as fit); a launch takes as
     // much as the LDS leaves at its occupancy, up to all JC jets (list_fit).
@@ -475,7 +482,7 @@ struct Caps {
     // (99%: 123), the extended one 47 (83), a selection without cuts all 320.
     // (The extended schema at two events per lane runs one 512-thread workgroup
     // per CU whatever its list.)
-    static constexpr int CAP_MIN = EXT ? (EVPL == 1 ? 128 : 576) : (EVPL == 1 ? 192 : 256);
+    static constexpr int CAP_MIN = EXT ? (EVPL == 1 ? 128 : 512) : (EVPL == 1 ? 128 : 256);
 };
 
 template <bool P>
@@ -507,7 +514,7 @@ struct Cand<TL, true> {
 template <typename T, int EVPL, bool EXT, bool LK>
 constexpr int list_bytes(int cap) {
     const int list = cap * static_cast<int>(sizeof(Cand<lds_t<T, EVPL, EXT>, LK>) + (EXT ? 1 : 0));
-    const int pre = (Caps<EVPL, EXT>::JC + 1) * static_cast<int>(sizeof(cpre_t<EXT>));
+    const int pre = (Caps<EVPL, EXT, LK>::JC + 1) * static_cast<int>(sizeof(cpre_t<EXT>));
     return ((list > pre ? list : pre) + 15) & ~15;
 }
 
@@ -517,7 +524,7 @@ constexpr int list_bytes(int cap) {
 // electrons.
 template <typename T, int EVPL, bool EXT, bool LK, bool MS>
 struct WaveLds {
-    using C = Caps<EVPL, EXT>;
+    using C = Caps<EVPL, EXT, LK>;
     using TL = lds_t<T, EVPL, EXT>;
     // selected muons, compacted in tile order (+2 padding), then (EXT) the
     // selected electrons likewise from index EO
@@ -775,8 +782,8 @@ template <typename T, bool EXT, int WAVES, int EVPL, bool LDSH, bool MS, bool DB
 __global__ __launch_bounds__(64 * WAVES)
     __attribute__((amdgpu_waves_per_eu(MS || (EVPL == 2 && EXT) ? 2 : (EXT || LK || EVPL == 2 ? 4 : 6)))) void
     pipeline_kernel(PipeArgs P) {
-    using C = Caps<EVPL, EXT>;
-    constexpr int TW = C::TW, JK = C::JK, MK = C::MK, EK = C::EK;
+    using C = Caps<EVPL, EXT, LK>;
+    constexpr int TW = C::TW, JK = C::JK, MK = C::MK, MX = C::MX, EK = C::EK;
     __shared__ WaveLds<T, EVPL, EXT, LK, MS> wl[WAVES];
     using TL = typename WaveLds<T, EVPL, EXT, LK, MS>::TL;
     // per workgroup: [sumw | sumw2 (LK) | counts (u32) | edges | scales | candidate lists]
@@ -1100,7 +1107,29 @@ __global__ __launch_bounds__(64 * WAVES)
                             }
                         });
                     } else {
-                        compact<MK, false>(sel, meta, mphi, lane, L.seta, L.sphi, L.u.p.mpre);
+                        int ns = compact<MK, false>(sel, meta, mphi, lane, L.seta, L.sphi, L.u.p.mpre);
+                        if (MX > 0 && __builtin_expect(nm > 64 * MK, 0)) {
+                            // the muons beyond the registers, from memory
+                            const uint32_t es = sizeof(T), mb_ = static_cast<uint32_t>(nm) * es;
+                            const int m = lane + 64 * MK;
+                            const uint32_t rpt = buf_raw<T>(buf_span(static_cast<const T *>(D.mpt) + B.M0, mb_), m);
+                            const uint32_t reta = buf_raw<T>(buf_span(static_cast<const T *>(D.meta) + B.M0, mb_), m);
+                            const uint32_t rphi = buf_raw<T>(buf_span(static_cast<const T *>(D.mphi) + B.M0, mb_), m);
+                            const uint32_t riso =
+                                has_iso ? buf_raw<T>(buf_span(static_cast<const T *>(D.miso) + B.M0, mb_), m) : 0u;
+                            const float eta = raw_f<T>(reta);
+                            const bool s = (m < nm) & (raw_f<T>(rpt) > mu_pt) & (fabsf(eta) < mu_abseta) &
+                                           (!has_iso | (raw_f<T>(riso) < mu_iso));
+                            const uint64_t bal = __ballot(s);
+                            const int before = bits_below(bal, ns);
+                            L.u.p.mpre[m] = static_cast<uint16_t>(before);
+                            if (s) {
+                                L.seta[before] = static_cast<TL>(eta);
+                                L.sphi[before] = static_cast<TL>(raw_f<T>(rphi));
+                            }
+                            ns += __popcll(bal);
+                            L.u.p.mpre[64 * (MK + 1)] = static_cast<uint16_t>(ns);
+                        }
                     }
                 }
                 if (EXT) {
