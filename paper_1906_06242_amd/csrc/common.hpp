@@ -206,6 +206,26 @@ __device__ __forceinline__ int hist_slot_lohi(float x, const float *E, int nbins
     return (x < E[s - 1] || x >= E[s]) ? bin_search(E, nbins, x) : s;
 }
 
+// Orders this wavefront's LDS accesses around the point (LDS executes one
+// wavefront's operations in issue order, so no wait is needed, only that the
+// compiler keeps the order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inclusive prefix sum over the wavefront (every lane active).
+__device__ __forceinline__ int wave_prefix_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+
 // Largest v over the wavefront (every lane active).
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #define HEPK_DPP_MAX(ctl, rows) \

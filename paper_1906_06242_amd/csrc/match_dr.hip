@@ -26,12 +26,6 @@ constexpr int MW = 4;    // wavefronts per workgroup
 constexpr int MKA = 8;   // a objects per lane: 512 per tile
 constexpr int MKB = 4;   // b objects per lane: 256 per tile
 
-__device__ __forceinline__ void wave_fence_dr() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Mask bytes of a tile are read as the aligned 4-byte words that hold them
 // (one load moves four masks; every word holds a byte of the range, so it
 // lies in the buffer's pages): mask_words issues the loads, mask_stage puts
@@ -177,7 +171,7 @@ __global__ __launch_bounds__(64 * MW) void match_dr_kernel(
         if (mask_b || mask_a) {
             const uint8_t *mbs = mask_b ? mask_stage<MBW>(mwb, mskb_s[wave], lane) : nullptr;
             const uint8_t *mas = mask_a ? mask_stage<MAW>(mwa, mska_s[wave], lane) : nullptr;
-            wave_fence_dr();
+            wave_sync();
             // a masked-out b gets eta = NaN: its dR^2 is NaN and never the minimum
 #pragma unroll
             for (int k = 0; k < MKB; ++k)
@@ -204,7 +198,7 @@ __global__ __launch_bounds__(64 * MW) void match_dr_kernel(
             }
             if (k < ae) ar[k] = pk;
         }
-        wave_fence_dr();
+        wave_sync();
         // ---- one lane per a object, slots in pairs: the pair's b ranges,
         // then the first two b objects of each range, each set of LDS reads
         // in flight together; only longer ranges loop over the rest.  A slot
@@ -262,7 +256,7 @@ __global__ __launch_bounds__(64 * MW) void match_dr_kernel(
                 }
             }
         }
-        wave_fence_dr();  // the next tile overwrites the staging
+        wave_sync();  // the next tile overwrites the staging
     }
 }
 
@@ -375,7 +369,7 @@ __global__ __launch_bounds__(64 * MW) void match_clean_kernel(
             run += __popcll(bal);
         }
         pre[64 * MKB] = static_cast<uint16_t>(run);
-        wave_fence_dr();
+        wave_sync();
         {
             const uint32_t b0 = pre[bb], bn = pre[bz] - b0;
             const uint32_t pk = b0 | (bn << 16);
@@ -386,7 +380,7 @@ __global__ __launch_bounds__(64 * MW) void match_clean_kernel(
             }
             if (k < ae) ar[k] = pk;
         }
-        wave_fence_dr();
+        wave_sync();
         // ---- one lane per a object, slots in pairs: the pair's b ranges,
         // then the first two b of each range, each set of LDS reads in flight
         // together; only longer ranges loop over the rest.  A slot past the
@@ -423,7 +417,7 @@ __global__ __launch_bounds__(64 * MW) void match_clean_kernel(
                 if (lane + 64 * k < na) clean[A0 + lane + 64 * k] = (rma[k] != 0u && !hit) ? 1 : 0;
             }
         }
-        wave_fence_dr();  // the next tile overwrites the staging
+        wave_sync();  // the next tile overwrites the staging
     }
 }
 

@@ -14,8 +14,8 @@
 //
 // Work decomposition.  Each wavefront owns tiles of TW = 64 * EVPL
 // consecutive events and works through them without waiting for the other
-// wavefronts of its workgroup (no workgroup barrier inside a tile: the four
-// or eight wavefronts of a workgroup only share the LDS histograms, updated
+// wavefronts of its workgroup (no workgroup barrier inside a tile: the up to
+// sixteen wavefronts of a workgroup only share the LDS histograms, updated
 // with atomics).  A launch covers whole datasets (one chunk each); every
 // workgroup takes an equal slice of their concatenated tiles, so uneven
 // datasets never unbalance the launch, and merges its LDS histograms into
@@ -27,7 +27,8 @@
 //      coalesced) -- into registers, and waits once;
 //   2. per query: muon (and electron) lanes evaluate the cuts; the selected
 //      leptons are compacted by wavefront ballot into LDS in tile order,
-//      with the count of selected leptons before each lepton;
+//      with the count of selected leptons before each lepton (muons beyond
+//      the MK per lane, up to one more each, are read from memory here);
 //   3. jet lanes mark the candidate jets (inside |eta|, pt above jet_pt at the
 //      largest energy any scale gives it) and write the number of candidates
 //      (and b-tagged candidates) before each jet; event lanes read both ends
@@ -36,7 +37,11 @@
 //      jets, so no other event can);
 //   4. the candidates of those events alone are compacted into LDS, and the
 //      cone test runs over that dense list, a lane per candidate: most jets
-//      of a tile never reach it (base selection: 86 of 320, with a b-tag 47);
+//      of a tile never reach it (base selection: 86 of 320, with a b-tag 47).
+//      The list's length is the launch's (list_fit); a tile with more
+//      candidates runs steps 4 and 5 in several passes over its events, each
+//      as many as fit, and an event longer than the list alone the per-event
+//      way;
 //   5. event lanes walk their candidates in order: ptv = pt * s, the jet cut,
 //      the count, the left-to-right float32 H_T, the maximum, the b-tag count;
 //      then the event cut and three fills into the workgroup's LDS
@@ -47,9 +52,9 @@
 // Steps 2-5 exchange data through the wavefront's own LDS region; a
 // wavefront's LDS operations complete in issue order, so only compiler
 // ordering fences are needed between them.  A tile whose objects exceed the
-// register capacity (a 3-sigma fluctuation of the paper's muon multiplicity,
-// always possible for arbitrary input) runs as smaller sub-tiles; a single
-// event beyond it is read straight from HBM, with the same arithmetic.
+// capacity (for 64 events 448 jets, 192 muons, 128 electrons) runs as smaller
+// sub-tiles; a single event beyond it is read straight from HBM, with the
+// same arithmetic.
 #pragma once
 
 #include <algorithm>
@@ -336,15 +341,6 @@ __device__ __forceinline__ void fill3(const HistSink<LDSH, W2> &sink, const QT &
         const int s = hist_slot_lohi(x, edges + Q.ebase[h], Q.nbins[h], Q.lo[h], Q.hi[h], Q.inv_w[h]);
         sink.add(base + (LDSH ? Q.lhoff[h] : Q.ghoff[h]) + s, w);
     }
-}
-
-// Orders this wavefront's LDS accesses around the point (LDS executes one
-// wavefront's operations in issue order, so no wait is needed, only that the
-// compiler keeps the order).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Value of x in lane l (l uniform).
@@ -711,17 +707,6 @@ __device__ __forceinline__ int bits_below(uint64_t m, int base) {
 __device__ __forceinline__ uint64_t lane_u64(uint32_t x, int l) {
     const uint32_t lo = __builtin_amdgcn_readlane(x, l), hi = __builtin_amdgcn_readlane(x, l + 1);
     return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
-// Inclusive prefix sum over the wavefront (every lane active).
-__device__ __forceinline__ int wave_prefix_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
 }
 
 __device__ __forceinline__ void or_u64(uint64_t *p, uint64_t v) {

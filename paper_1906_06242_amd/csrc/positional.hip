@@ -171,11 +171,6 @@ __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__rest
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Obj *ob = obj_s[wave];
-    auto sync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
     const int64_t n_tiles = ceil_div(n_events, 64);
     const int64_t step = static_cast<int64_t>(gridDim.x) * (PB / 64);
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * (PB / 64) + wave; t < n_tiles; t += step) {
@@ -226,7 +221,7 @@ __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__rest
                 for (int k = 0; k < H; ++k)
                     ob[lane + 64 * (k + H * h)] = Obj{raw_f<T>(p[k]), os_code(m[k], static_cast<int32_t>(c[k]))};
             }
-            sync();
+            wave_sync();
             if (lane < ne) {
                 const int a0 = static_cast<int32_t>(o0 - static_cast<uint32_t>(A));
                 const int a1 = static_cast<int32_t>(o1 - static_cast<uint32_t>(A));
@@ -244,9 +239,9 @@ __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__rest
                     ob[b.bn].code = 3u;
                 }
             }
-            sync();
+            wave_sync();
             for (int i = lane; i < n; i += 64) out[A + i] = ob[i].code == 3u ? 1 : 0;
-            sync();  // the next (part of a) tile overwrites the staging
+            wave_sync();  // the next (part of a) tile overwrites the staging
             e0 = e1;
         }
     }

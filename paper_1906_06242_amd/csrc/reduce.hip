@@ -34,12 +34,6 @@ __device__ __forceinline__ int64_t wave_scan(int64_t v) {
     return v;
 }
 
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Running reduction of one event.
 template <int OP>
 struct Acc {
@@ -172,7 +166,7 @@ __global__ __launch_bounds__(RB) void reduce_kernel(const int64_t *__restrict__ 
             }
             const uint8_t *ms = reinterpret_cast<const uint8_t *>(msw) + s;
             const bool all = obj_mask == nullptr;
-            wave_fence();
+            wave_sync();
             const int b0 = static_cast<int>(a0), b1 = static_cast<int>(a1);  // within the tile's 512
             if (take) {
                 // two objects per step (both LDS reads in flight), in order
@@ -185,7 +179,7 @@ __global__ __launch_bounds__(RB) void reduce_kernel(const int64_t *__restrict__ 
                 }
                 if (k < b1) r.add(OP != R_COUNT ? vs[k] : 0.0f, all || ms[k] != 0, k - b0);
             }
-            wave_fence();  // the next tile overwrites the staging
+            wave_sync();  // the next tile overwrites the staging
         } else if (event_range(), take) {
             for (int64_t k = a0; k < a1; ++k)
                 r.add(OP != R_COUNT ? ldf(content, A + k) : 0.0f, !obj_mask || obj_mask[A + k] != 0,

@@ -96,12 +96,6 @@ __global__ __launch_bounds__(256) void p4_vec4_kernel(const float *__restrict__ 
     }
 }
 
-__device__ __forceinline__ void wave_fence_t() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Running best triplet of one event.
 struct Best {
     float d = INFINITY, m = __builtin_nanf("");
@@ -289,7 +283,7 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             run += __popcll(bal);
         }
         if (lane == 0) L.pre[nobj] = static_cast<uint16_t>(run);
-        wave_fence_t();
+        wave_sync();
         // 2. per event: first selected object, count, triplets; prefix sums
         // over the tile
         int s0 = 0, nn = 0;
@@ -297,19 +291,13 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             s0 = L.pre[a0];
             nn = L.pre[a1] - s0;
         }
-        int incl = act ? c3(nn) : 0;
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);  // row_shr:1
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);  // row_shr:2
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);  // row_shr:4
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);  // row_shr:8
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15
-        incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);  // row_bcast:31
+        const int incl = wave_prefix_sum(act ? c3(nn) : 0);
         L.tp[lane + 1] = incl;
         if (lane == 0) L.tp[0] = 0;
         L.s0[lane] = s0;
         L.n[lane] = nn;
         L.key[lane] = ~0ull;
-        wave_fence_t();
+        wave_sync();
         // 3-4. this lane's share of the tile's triplets
         const int T = __builtin_amdgcn_readlane(incl, 63);
         const int t0 = static_cast<int>(static_cast<uint32_t>(T) * static_cast<uint32_t>(lane) >> 6);
@@ -377,7 +365,7 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             }
             merge();
         }
-        wave_fence_t();
+        wave_sync();
         // 5. each event's minimum back to its triplet and mass
         if (act) {
             const uint64_t key = L.key[lane];
@@ -398,7 +386,7 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
             out_idx[3 * e + 1] = bj;
             out_idx[3 * e + 2] = bk;
         }
-        wave_fence_t();  // the next tile overwrites the staging
+        wave_sync();  // the next tile overwrites the staging
     }
 }
 
