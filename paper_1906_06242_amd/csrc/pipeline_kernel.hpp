@@ -465,7 +465,7 @@ struct Caps {
     // One more slot of muons that no register holds: read per query in the
     // tiles that have so many (at two muons per event half of the tiles do).
     // 3e6 events of 2.3 muons, those tiles split in two / with the slot: base
-    // 109 / 77 us, eight queries 516 / 356, extended 165 / 108.  A third
+    // 109 / 76 us, eight queries 516 / 353, extended 170 / 109.  A third
     // register slot would leave five wavefronts per SIMD instead of six.  The
     // lookup kernels, whose LDS is full, split.
     static constexpr int MX = LK ? 0 : 1;
@@ -476,8 +476,8 @@ struct Caps {
     // much as the LDS leaves at its occupancy, up to all JC jets (list_fit).
     // The base selection lists 86 candidates of a 64-event tile on average
     // (99%: 123), the extended one 47 (83), a selection without cuts all 320.
-    // (The extended schema at two events per lane runs one 512-thread workgroup
-    // per CU whatever its list.)
+    // (The extended schema at two events per lane runs eight wavefronts per CU
+    // whatever its list.)
     static constexpr int CAP_MIN = EXT ? (EVPL == 1 ? 128 : 512) : (EVPL == 1 ? 128 : 256);
 };
 
@@ -741,20 +741,23 @@ __device__ __forceinline__ int compact(const bool (&sel)[K], const float (&eta)[
 
 // MS: the plan has queries with several jet-energy scales (every query then
 // takes the scale-group walk of step 5; otherwise every query has one scale).
-// What bounds it: VALU issue and, per wavefront, the wait for a tile's loads
-// and a dozen dependent LDS round trips; so the dense list (fewer
-// instructions per tile: base 545 -> 465, 20 scales 1630 -> 1340) and as many
-// wavefronts as registers and LDS allow.  The base schema at one scale gets six
-// per SIMD (at most 80 VGPRs; five took 5% longer per 1e7 events, seven, which
-// 256-thread workgroups would get, 24%), the others four.  Before and after the dense
-// list: 1e7 base events 210 -> 203 us, eight queries over 6.25e6 events 764 ->
-// 555 us, 20 scales over 2e7 float16 events 1031 -> 900 us, 20 shifts with
-// lookup weights over 1e7 1467 -> 783 us (203, 538, 799 and 680 us with the
-// shorter fills, the flat merge and the bucket tables; there also two wavefronts per SIMD
-// -> four: the list needs 3.9 KB of LDS per wavefront where all jets took
-// 8 KB, and the shift and scale-factor searches run for listed jets and
-// selected muons only).  Loading the next tile into the registers while the
-// list is worked on was slower at four wavefronts (280 us against 240).
+// What bounds it: VALU issue (79% of the issue slots with 20 scales, with or
+// without lookups, 67% with eight queries, 59% with one) and, per wavefront,
+// the wait for a tile's loads and a dozen dependent LDS round trips; so the
+// dense list, which cut the instructions per tile (base 545 -> 468, 20 scales
+// 1630 -> 1227), and as many wavefronts as registers and LDS allow.  Asked for
+// per SIMD: six in the base schema at one scale and one event per lane (at
+// most 80 VGPRs; five took 5% longer per 1e7 events, seven, which 256-thread
+// workgroups would get, 24%); four in the extended one, with lookups and in
+// the base schema at two events; two with several scales, which the launch
+// bound of their default 1024 threads raises to four, and in the extended
+// schema at two events (four spills).  Before the list / now: 1e7 base events
+// 210 / 200 us, eight queries over 6.25e6 events 764 / 518, 20 scales over 2e7
+// float16 events 1031 / 795, 20 shifts with lookup weights over 1e7 1467 /
+// 662 (there also two wavefronts per SIMD -> four, and shift and scale-factor
+// searches for listed jets and selected muons only).  Loading the next tile
+// into the registers while the list is worked on was slower at four
+// wavefronts (280 us against 240).
 // DBG: also write every event's per-scale record (counts, H_T, leading pt,
 // whether the event was walked and whether it passed) to P.rec -- the
 // intermediate values of the pass, for checking them one by one.  Product

@@ -153,7 +153,7 @@ __device__ __forceinline__ OsPair os_pair(int lane, int64_t n, G &&get) {
 // 7.5e6 muons in 5e6 events (115 MB; floor 17 us).  Tiles with more objects
 // than the staging holds run in parts.  Parts of few events, which would leave
 // most lanes idle, are taken event by event by the whole wavefront, straight
-// from HBM (events of 300 objects 2500 -> 180 us per 1.5e7 objects, of 2000
+// from HBM (events of 300 objects 2500 -> 208 us per 1.5e7 objects, of 2000
 // 20 -> 0.87 ms per 2e7).
 constexpr int kOsSlots = 8;   // objects per lane staged for one tile
 constexpr int kOsFew = 8;     // events of a part that go one by one
@@ -173,30 +173,30 @@ __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__rest
     Obj *ob = obj_s[wave];
     const int64_t n_tiles = ceil_div(n_events, 64);
     const int64_t step = static_cast<int64_t>(gridDim.x) * (PB / 64);
+    // the part [e0, e1) of a tile that ends at t1: its events (at least one),
+    // and its objects [A, B)
+    auto part = [&](int64_t e0, int64_t t1, int64_t &A, int64_t &B) {
+        int ne = static_cast<int>(t1 - e0);
+        A = as_const(off)[e0];
+        B = as_const(off)[t1];
+        while (ne > 1 && B - A > 64 * kOsSlots) {
+            ne = (ne + 1) / 2;
+            B = as_const(off)[e0 + ne];
+        }
+        return ne;
+    };
+    bool few = false;
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * (PB / 64) + wave; t < n_tiles; t += step) {
         const int64_t t1 = min<int64_t>(t * 64 + 64, n_events);
-        for (int64_t e0 = t * 64; e0 < t1;) {
-            int64_t e1 = t1;
-            const int64_t A = as_const(off)[e0];
-            int64_t B = as_const(off)[e1];
-            while (e1 - e0 > 1 && B - A > 64 * kOsSlots) {
-                e1 = e0 + (e1 - e0 + 1) / 2;
-                B = as_const(off)[e1];
-            }
-            if (__builtin_expect(e1 - e0 <= kOsFew, 0)) {
-                for (int64_t e = e0; e < e1; ++e) {
-                    const int64_t a0 = as_const(off)[e], m = as_const(off)[e + 1] - a0;
-                    const OsPair b = os_pair(lane, m, [&](int64_t i, uint32_t &code, float &p) {
-                        code = os_code(om ? om[a0 + i] : 1u, q[a0 + i]);
-                        p = ldf(pt, a0 + i);
-                    });
-#pragma unroll 1
-                    for (int64_t i = lane; i < m; i += 64) out[a0 + i] = (b.p >= 0 && (i == b.p || i == b.n)) ? 1 : 0;
-                }
-                e0 = e1;
+        for (int64_t e0 = t * 64, e1; e0 < t1; e0 = e1) {
+            int64_t A, B;
+            const int ne = part(e0, t1, A, B);
+            e1 = e0 + ne;
+            if (__builtin_expect(ne <= kOsFew, 0)) {
+                few = true;  // below
                 continue;
             }
-            const int n = static_cast<int>(B - A), ne = static_cast<int>(e1 - e0);
+            const int n = static_cast<int>(B - A);
             const buf_t bo = buf_span(off + e0, static_cast<uint32_t>(ne + 1) * 8u);
             const uint32_t o0 = buf_u32<kBufNt>(bo, lane * 8), o1 = buf_u32<kBufNt>(bo, lane * 8 + 8);
             const buf_t bp = buf_span(pt + A, static_cast<uint32_t>(n) * sizeof(T));
@@ -242,7 +242,27 @@ __global__ __launch_bounds__(PB) void opposite_sign_kernel(const int64_t *__rest
             wave_sync();
             for (int i = lane; i < n; i += 64) out[A + i] = ob[i].code == 3u ? 1 : 0;
             wave_sync();  // the next (part of a) tile overwrites the staging
-            e0 = e1;
+        }
+    }
+    if (!few) return;
+    // the parts of few events (a loop of their own: beside the tiles their
+    // registers and addresses cost 5e6 ordinary events 4%)
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * (PB / 64) + wave; t < n_tiles; t += step) {
+        const int64_t t1 = min<int64_t>(t * 64 + 64, n_events);
+        for (int64_t e0 = t * 64, e1; e0 < t1; e0 = e1) {
+            int64_t A, B;
+            const int ne = part(e0, t1, A, B);
+            e1 = e0 + ne;
+            if (ne > kOsFew) continue;
+            for (int64_t e = e0; e < e1; ++e) {
+                const int64_t a0 = as_const(off)[e], m = as_const(off)[e + 1] - a0;
+                const OsPair b = os_pair(lane, m, [&](int64_t i, uint32_t &code, float &p) {
+                    code = os_code(om ? om[a0 + i] : 1u, q[a0 + i]);
+                    p = ldf(pt, a0 + i);
+                });
+#pragma unroll 1
+                for (int64_t i = lane; i < m; i += 64) out[a0 + i] = (b.p >= 0 && (i == b.p || i == b.n)) ? 1 : 0;
+            }
         }
     }
 }

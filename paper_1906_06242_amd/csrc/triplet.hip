@@ -198,9 +198,9 @@ __global__ __launch_bounds__(TB) void best_triplet_kernel(const int64_t *__restr
     // words: tile-relative differences are exact modulo 2^32) and its objects,
     // buffer loads over exactly the tile's ranges (0 past their ends, no
     // per-slot branch; none for a dense tile), all in flight and waited for
-    // once: 175 -> 159 us on 3e6 events with the 32-bit ranks (850 VALU
-    // instructions per tile instead of 1085).  (Issuing them while the tile before is searched gained nothing:
-    // the search is bound by VALU issue.)
+    // once: 175 -> 159 us on 3e6 events with the 32-bit ranks (813 VALU
+    // instructions per tile instead of 1085: 39% of the issue slots).  (Issuing
+    // them while the tile before is searched gained nothing.)
     struct Raw {
         uint32_t o0, o1;
         uint32_t x[TK], y[TK], z[TK], e[TK], m[TK];
